@@ -460,6 +460,23 @@ static aol_status plan_build_band(aol_plan* pl, int xreps, int seg) {
   pl->bslots = slots;
   pl->blds = (size_t)lds;
   pl->bgrid = wg * cus;
+  if (pl->strips.cls < 0) {
+    if ((st = build_strip_tables(pl->hf, pl->vf, pl->elem, pl->strips))) return st;
+    pl->sedges = false;
+    for (int i = 0; i < pl->n_planes && pl->strips.cls >= 0; ++i) {
+      const aol_plane_desc& d = pl->planes[i];
+      if (!build_strip_stream(pl->strips, d.height, d.width, d.in_pitch, d.out_pitch, pl->sstreams[i])) pl->strips.cls = -1;
+      pl->sstreams[i].ptr = i;
+      pl->sedges = pl->sedges || strip_edges(pl->strips, pl->sstreams[i]);
+    }
+    for (int f = 0; f < kStripForms && pl->strips.cls >= 0; ++f) {
+      if (f == kStripWide && pl->sedges) pl->strips.wnb[f] = 0;  // (no such instance)
+      if (!pl->strips.wnb[f]) continue;
+      if ((e = strip_prepare(pl->elem, pl->strips.cls, f, pl->sedges, pl->strips.lds[f])) != hipSuccess)
+        return hip_fail(e, "strip kernel attributes");
+    }
+  }
+  pl->cus = cus;
   pl->use_band = true;
   return AOL_OK;
 }
@@ -600,6 +617,86 @@ static const aol_plan::BandSched* band_pick_sched(const aol_plan* plan, int n_fr
   return &plan->bsched.back();
 }
 
+// Workgroups of one kernel launch at most (a grid holds fewer than 2^32 threads).
+static constexpr int kStripMaxGrid = 1 << 22;
+
+static int64_t strip_wgs(const aol_plan* plan, int form, int segb) {
+  int64_t wgs = 0;
+  for (int i = 0; i < plan->n_planes; ++i) {
+    const StripStream& S = plan->sstreams[i];
+    wgs += (int64_t)((S.nbh + plan->strips.wnb[form] - 1) / plan->strips.wnb[form]) * ((S.nbv + segb - 1) / segb);
+  }
+  return wgs;
+}
+
+// Form and vertical blocks per segment of a launch over n frames (I420
+// 1920x1080 at 3/8 unless said):
+//  * eight waves, segments of about 512 input lines (256 of 16-bit elements),
+//    where that makes four rounds of resident workgroups: a wider workgroup
+//    reads fewer lines twice at its sides (300 frames: u8 0.232 against 0.239
+//    ms, bf16 0.480 against 0.507);
+//  * else four waves, the segments halved down to four blocks until the
+//    workgroups make one round (24 frames of 3840x2160 at 2/3: 18 blocks 0.107
+//    ms, 9 0.112, 4 0.131; 16 of 1280x720 fp16 at 1/2: 4 blocks 14.9 us, 2 16.5:
+//    every workgroup pays its set-up), and down to one block while there are
+//    fewer workgroups than compute units (one frame: the kernel takes 8.5 us
+//    with one block, 10.3 with two, 13.1 with four).
+static int strip_form(const aol_plan* plan, int n_frames, const aol_plan::BandSched* sc, int* segb) {
+  const StripTables& T = plan->strips;
+  int sb = std::max(1, sc->seg * T.p_v / 16);
+  const int wide = std::max(1, plan->elem == kU8 ? sb : sb / 2);
+  if (T.wnb[kStripWide] && plan->bseg == 0 && strip_wgs(plan, kStripWide, wide) * n_frames >= 4 * 2 * (int64_t)plan->cus) {
+    *segb = wide;
+    return kStripWide;
+  }
+  if (plan->bseg == 0) {
+    while (sb > 4 && strip_wgs(plan, kStripUsual, sb) * n_frames < 4 * (int64_t)plan->cus) sb = std::max(4, sb / 2);
+    while (sb > 1 && strip_wgs(plan, kStripUsual, sb) * n_frames < plan->cus) --sb;
+  }
+  *segb = sb;
+  return kStripUsual;
+}
+
+static aol_status run_strips(aol_plan* plan, int32_t n_frames, const void* const* d_in, const int64_t* in_fs,
+                             void* const* d_out, const int64_t* out_fs, hipStream_t stream) {
+  StripLaunch L;
+  memset(&L, 0, sizeof L);
+  L.n_planes = plan->n_planes;
+  L.filter = plan->strips.host;
+  int segb = 1;
+  const int form = strip_form(plan, n_frames, band_pick_sched(plan, n_frames), &segb);
+  int64_t wgs = 0, bytes = 0;
+  for (int i = 0; i < plan->n_planes; ++i) {
+    StripStream& S = L.st[i];
+    S = plan->sstreams[i];
+    bytes += (int64_t)n_frames * ((int64_t)S.h * S.w * (plan->elem == kU8 ? 1 : 2) + (int64_t)S.mh * S.mw * (plan->elem == kU8 ? 1 : 4));
+    strip_set_segments(S, plan->strips.wnb[form], segb);
+    S.wg_base = (int32_t)wgs;
+    wgs += (int64_t)S.wgx * S.nseg;
+    L.ptrs[2 * i] = d_in[i];
+    L.ptrs[2 * i + 1] = d_out[i];
+    L.fstride[2 * i] = n_frames > 1 ? in_fs[i] : 0;
+    L.fstride[2 * i + 1] = n_frames > 1 ? out_fs[i] : 0;
+  }
+  if (wgs * n_frames > INT_MAX) return fail(AOL_ERR_UNSUPPORTED, "too many units in one launch");
+  const int total = (int)(wgs * n_frames);
+  L.wgs_per_frame = (int32_t)wgs;
+  L.mg_wgs = strip_magic(L.wgs_per_frame);
+  // Workgroups that share lines (neighbours in a row, the segments of a
+  // column) on one XCD, for its L2; but a launch well beyond the memory-side
+  // cache (256 MiB) runs all XCDs through the same frames (24 frames of
+  // 3840x2160, 431 MB: 0.107 against 0.111 ms; 300 of 1920x1080, 1065 MB:
+  // 0.239 against 0.232).
+  L.by_xcd = total <= kStripMaxGrid && bytes < (512LL << 20) ? 1 : 0;
+  for (int first = 0; first < total; first += kStripMaxGrid) {
+    L.first = first;
+    hipError_t e = strip_launch(plan->elem, plan->strips.cls, form, plan->sedges, L,
+                                std::min(total - first, kStripMaxGrid), plan->strips.lds[form], stream);
+    if (e != hipSuccess) return hip_fail(e, "strip kernel launch");
+  }
+  return ok();
+}
+
 static aol_status run_fused(aol_plan* plan, int32_t n_frames, const void* const* d_in, const int64_t* in_fs,
                             void* const* d_out, const int64_t* out_fs, hipStream_t stream, int out_es) {
   if (n_frames < 0) return fail(AOL_ERR_INVALID, "n_frames < 0");
@@ -641,6 +738,7 @@ static aol_status run_fused(aol_plan* plan, int32_t n_frames, const void* const*
   }
   const int64_t total = tiles * n_frames;
   if (total > INT_MAX || tiles > INT_MAX) return fail(AOL_ERR_UNSUPPORTED, "too many tiles in one launch");
+  if (plan->use_band && plan->strips.cls >= 0) return run_strips(plan, n_frames, d_in, in_fs, d_out, out_fs, stream);
   if (plan->use_band) {
     BandLaunch L;
     memset(&L, 0, sizeof L);

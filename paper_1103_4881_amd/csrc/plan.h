@@ -7,6 +7,7 @@
 #include "aolmi.h"
 #include "band_host.h"
 #include "common.h"
+#include "strip_host.h"
 
 namespace aol {
 
@@ -64,6 +65,11 @@ struct aol_plan {
     DeviceBuf d_units;
   };
   std::vector<BandSched> bsched;
+  // strip kernel (runs the band schedule; strips.cls < 0: not available)
+  StripTables strips;
+  StripStream sstreams[kMaxPlanes];
+  bool sedges = false;  // some plane's lines are not whole 16-byte chunks
+  int cus = 0;  // compute units of the device
   std::string sched_json;  // text returned by aol_plan_schedule
   bool split = false;
   DeviceBuf d_hb, d_vb, d_hfrag, d_vfrag;

@@ -1,0 +1,46 @@
+// Host-side construction of the strip kernel's descriptors.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <vector>
+
+#include "common.h"
+#include "strip.h"
+
+namespace aol {
+
+// One filter pair's device tables for the strip kernel.
+struct StripTables {
+  int elem = kU8;
+  int cls = -1;       // 2 * class + split; -1: beyond the kernel's instances
+  int wnb[kStripForms] = {0, 0};  // strips per workgroup at most, by form (0: no instance)
+  int col0 = 0, line0 = 0;
+  int p_v = 1;
+  size_t lds[kStripForms] = {0, 0};  // bytes of a workgroup, by form
+  StripFilter host{};
+  DeviceBuf d_filter, d_hfrag, d_vfrag, d_bias;
+};
+
+// AOL_OK with out.cls = -1 when no instance serves the filters.
+aol_status build_strip_tables(const FilterHost& hf, const FilterHost& vf, int elem, StripTables& out);
+
+// Descriptor of one plane or stream (segments: see strip_set_segments).
+// False for planes of 4 GiB or more (the kernel's lane offsets are 32-bit).
+bool build_strip_stream(const StripTables& t, int64_t h, int64_t w, int64_t in_pitch, int64_t out_pitch,
+                        StripStream& S);
+
+uint32_t strip_magic(int d);  // floor(2^32 / d) + 1 (0 for 1)
+
+// A line of the plane is not whole 16-byte chunks.
+bool strip_edges(const StripTables& t, const StripStream& S);
+
+// Workgroups of at most wnb strips (evened out over a row) and segments of at
+// most segb vertical blocks.
+void strip_set_segments(StripStream& S, int wnb, int segb);
+
+// edges: some line of the launch is not whole 16-byte chunks.
+hipError_t strip_prepare(int elem, int cls, int form, bool edges, size_t lds_bytes);
+hipError_t strip_launch(int elem, int cls, int form, bool edges, const StripLaunch& L, int grid, size_t lds_bytes,
+                        hipStream_t stream);
+
+}  // namespace aol
