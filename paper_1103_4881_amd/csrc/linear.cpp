@@ -15,6 +15,8 @@ using namespace aol;
 struct aol_linear_plan {
   LinearArgs args{};
   LinearStage stage{};  // staged form (stage.ppt == 0: not available)
+  LinearBox box{};      // matrix-core form (box.use == 0: not available)
+  LinearPack pack{};    // packed form (pack.inst == 0: not available)
   int nout = 1;  // kernel instance: output pattern elements rounded up to 1, 2, 3, 4, 6, 8, 9, 12 or 16
   DeviceBuf d_tab;
 };
@@ -221,6 +223,260 @@ void plan_stage(const LinearArgs& a, int nout, const std::vector<int32_t>& ioff,
       if (ooff[(size_t)j] >= st.ob[g] && ooff[(size_t)j] < (int64_t)st.ob[g] + Po) og[(size_t)j] = g;
 }
 
+// The packed form, or inst = 0 when it does not apply: no point's pattern
+// leaves its array before the modulo, the last dim's flat strides and the
+// pattern's bytes per point make one of kLinPacks' shapes, each stream's bytes
+// in one order.
+void plan_pack(const LinearArgs& a, const aol_tiler* in, const aol_tiler* out, const int16_t* weights,
+               const int32_t* bias, int n_in, int n_out, LinearPack& p) {
+  memset(&p, 0, sizeof p);
+  if (n_in > kLinPackSlots || n_out > kLinPackSlots) return;
+  const int last = a.rr - 1;
+  // flat strides per repetition dim and flat origin, from the tilers' own (signed) numbers
+  int64_t fs[2][kLinRank], base[2], off[2][kLinPackSlots];
+  for (int side = 0; side < 2; ++side) {
+    const aol_tiler* t = side ? out : in;
+    const int np = side ? n_out : n_in;
+    for (int k = 0; k < a.rr; ++k) fs[side][k] = 0;
+    base[side] = 0;
+    for (int i = 0; i < np; ++i) off[side][i] = 0;
+    int64_t st = 1;
+    for (int d = t->array_rank - 1; d >= 0; --d) {
+      const int64_t S = t->array_shape[d], o = pmod64(t->origin[d], S);
+      int64_t lo = o, hi = o, flo = 0, fhi = 0;
+      for (int k = 0; k < a.rr; ++k) {
+        if (std::abs(t->paving[d][k]) > S) return;  // (the spans below stay far inside int64)
+        const int64_t span = t->paving[d][k] * (t->rep_shape[k] - 1);
+        (span < 0 ? lo : hi) += span;
+        fs[side][k] += t->paving[d][k] * st;
+      }
+      for (int i = 0; i < np; ++i) {
+        int64_t f[AOL_MAX_RANK];
+        fitting_offsets(t, i, f);
+        flo = std::min(flo, f[d]);
+        fhi = std::max(fhi, f[d]);
+        if (std::abs(f[d]) > S) return;
+        off[side][i] += f[d] * st;
+      }
+      if (lo + flo < 0 || hi + fhi >= S) return;
+      base[side] += o * st;
+      st *= S;
+    }
+  }
+  int slot[2][kLinPackSlots];
+  for (int v = 0; v < 2 && !p.inst; ++v) {
+    const LinearPackShape sh = kLinPacks[v];
+    bool ok = fs[0][last] == sh.si && fs[1][last] == sh.so && n_in == sh.si * sh.ni && n_out == sh.so * sh.no;
+    for (int side = 0; side < 2 && ok; ++side) {
+      const int S = side ? sh.so : sh.si, np = side ? n_out : n_in;
+      std::vector<std::pair<int64_t, int>> el;
+      for (int i = 0; i < np; ++i) el.push_back({off[side][i], i});
+      std::sort(el.begin(), el.end());
+      for (int q = 0; q < np; ++q) {
+        ok = ok && el[(size_t)q].first == el[(size_t)(q / S * S)].first + q % S;
+        slot[side][el[(size_t)q].second] = q;
+        if (q % S == 0) (side ? p.bo : p.bi)[q / S] = base[side] + el[(size_t)q].first;
+      }
+    }
+    if (ok) p.inst = v + 1;
+  }
+  if (!p.inst) return;
+  for (int j = 0; j < n_out; ++j) {
+    for (int i = 0; i < n_in; ++i) p.w[slot[1][j]][slot[0][i]] = weights[(size_t)j * n_in + i];
+    p.bias[slot[1][j]] = (bias ? bias[j] : 0) + 128;
+  }
+  // the run: the last dim, and those before it that continue it in both arrays
+  int64_t len = a.R[last];
+  int k = last - 1;
+  while (k >= 0 && fs[0][k] == fs[0][last] * len && fs[1][k] == fs[1][last] * len && len * a.R[k] < (1LL << 30)) {
+    len *= a.R[k];
+    --k;
+  }
+  p.len = (int32_t)len;
+  const int per = kLinThreads * kLinPackPoints;
+  p.groups = (int32_t)((len + per - 1) / per);
+  p.mg_groups = magic((uint32_t)p.groups);
+  p.n_outer = k + 1;
+  int64_t blocks = p.groups;
+  for (int d = 0; d <= k; ++d) {
+    p.R[d] = a.R[d];
+    p.mg_R[d] = magic((uint32_t)a.R[d]);
+    p.fi[d] = fs[0][d];
+    p.fo[d] = fs[1][d];
+    blocks *= a.R[d];
+  }
+  if (blocks >= (1LL << 24)) p.inst = 0;
+}
+
+// The matrix-core form's layout and tables (appended to tab), or use = 0 when
+// it does not apply: more than kLinStageMaxIn pattern elements (smaller
+// patterns have the staged form, or keep too little of a product busy), no two
+// on one position and none reaching as far as an axis is long, a box that fits
+// kLinBoxLds and is no longer than twice an axis, at most
+// kLinBoxSteps K-steps, weights within two int8 parts.
+void plan_box(const LinearArgs& a, const aol_tiler* in, const int16_t* weights, const int32_t* bias, int n_in,
+              int n_out, LinearBox& b, std::vector<int32_t>& tab) {
+  memset(&b, 0, sizeof b);
+  const int last = a.rr - 1, last_d = a.ra - 1;
+  if (n_in <= kLinStageMaxIn) return;
+  for (int j = 0; j < n_out; ++j) {  // the sums over x - 128 stay in int32 too
+    int64_t m = 128 + (bias ? std::abs((int64_t)bias[j]) : 0);
+    for (int i = 0; i < n_in; ++i) m += 512 * std::abs((int64_t)weights[(size_t)j * n_in + i]);
+    if (m >= (1LL << 31)) return;
+  }
+  for (int d = 0; d < a.ra; ++d)
+    if (a.lo[d] <= -a.S[d] || a.hi[d] >= a.S[d]) return;
+  int32_t Ps[kLinRank][kLinRank];  // pavings, signed, nearest zero
+  for (int d = 0; d < a.ra; ++d)
+    for (int k = 0; k < a.rr; ++k) Ps[d][k] = (int64_t)a.P[d][k] * 2 > a.S[d] ? a.P[d][k] - a.S[d] : a.P[d][k];
+  bool split = false;
+  for (int64_t i = 0; i < (int64_t)n_in * n_out; ++i) {
+    if (weights[i] < -128 || weights[i] > 127) split = true;
+    if (weights[i] < -64 - 128 * 128 || weights[i] > 63 + 127 * 128) return;  // lo + 128 * hi, both int8
+  }
+  const int parts = split ? 2 : 1;
+  // the other dim of a block: the one with the smallest box
+  int64_t best = -1;
+  for (int kj = -1; kj < last; ++kj) {
+    if (kj < 0 && last > 0) continue;
+    int64_t ext[kLinRank], lo[kLinRank], bytes = 1;
+    bool fit = true;
+    for (int d = 0; d < a.ra; ++d) {
+      ext[d] = a.hi[d] - a.lo[d] + 1;
+      lo[d] = a.lo[d];
+      for (int k : {last, kj}) {
+        if (k < 0) continue;
+        const int64_t span = (int64_t)Ps[d][k] * (k == last ? kLinBoxX - 1 : kLinBoxY - 1);
+        ext[d] += span < 0 ? -span : span;
+        lo[d] += span < 0 ? span : 0;
+      }
+      fit = fit && ext[d] <= 2 * (int64_t)a.S[d];
+      if (d == last_d) ext[d] = (ext[d] + 15) / 16 * 16;
+      if (bytes * ext[d] > kLinBoxLds) fit = false;
+      if (fit) bytes *= ext[d];
+    }
+    if (!fit || (best >= 0 && bytes >= best)) continue;
+    best = bytes;
+    b.k_loop = kj;
+    for (int d = 0; d < a.ra; ++d) {
+      b.bn[d] = (int32_t)ext[d];
+      b.dlo[d] = (int32_t)pmod64(lo[d], a.S[d]);
+    }
+  }
+  if (best < 0) return;
+  const int kj = b.k_loop;
+  b.pitch = b.bn[last_d];
+  b.nch = b.pitch / 16;
+  b.rows = (int32_t)(best / b.pitch);
+  if ((int64_t)b.rows * b.nch >= 65536) return;
+  int64_t bst[kLinRank], s1 = 1;
+  for (int d = last_d; d >= 0; --d) {
+    bst[d] = s1;
+    s1 *= b.bn[d];
+  }
+  int64_t ls = 0, js = 0, corner = 0;  // corner: box position of the corner point's base
+  for (int d = 0; d < a.ra; ++d) {
+    ls += Ps[d][last] * bst[d];
+    if (kj >= 0) js += Ps[d][kj] * bst[d];
+    int64_t lo = a.lo[d];
+    for (int k : {last, kj}) {
+      if (k < 0) continue;
+      const int64_t span = (int64_t)Ps[d][k] * (k == last ? kLinBoxX - 1 : kLinBoxY - 1);
+      lo += span < 0 ? span : 0;
+    }
+    corner -= lo * bst[d];
+  }
+  b.lstep = (int32_t)ls;
+  b.jstep = (int32_t)js;
+  // chunks of 16 bytes that cover the pattern's elements, in order of position
+  std::vector<std::pair<int64_t, int>> el((size_t)n_in);
+  for (int i = 0; i < n_in; ++i) {
+    int64_t f[AOL_MAX_RANK], o = corner;
+    fitting_offsets(in, i, f);
+    for (int d = 0; d < a.ra; ++d) o += f[d] * bst[d];
+    el[(size_t)i] = {o, i};
+  }
+  std::sort(el.begin(), el.end());
+  for (int i = 1; i < n_in; ++i)
+    if (el[(size_t)i].first == el[(size_t)i - 1].first) return;
+  std::vector<int64_t> chunks;
+  std::vector<std::vector<std::pair<int, int>>> member;  // (byte of the chunk, element)
+  for (const auto& e : el) {
+    if (chunks.empty() || e.first >= chunks.back() + 16) {
+      chunks.push_back(e.first);
+      member.emplace_back();
+    }
+    member.back().push_back({(int)(e.first - chunks.back()), e.second});
+  }
+  b.steps = (int32_t)((chunks.size() + 3) / 4);
+  if (b.steps > kLinBoxSteps) return;
+  b.lds_roff = 4 * b.steps * 4;
+  b.lds_box = (b.lds_roff + b.rows * 4 + 15) / 16 * 16;
+  // (a chunk may reach 15 bytes past the box: weight zero there)
+  b.lds_bytes = (int32_t)((b.lds_box + best + 16 + 15) / 16 * 16);
+  if (b.lds_bytes > kLinBoxLds) return;
+  // weights in lane order: lane (g, m): output m, bytes of chunk 4 k + g
+  while (tab.size() % 4) tab.push_back(0);
+  b.t_w = (int32_t)tab.size();
+  std::vector<int8_t> w((size_t)b.steps * parts * 1024, 0);
+  for (size_t c = 0; c < chunks.size(); ++c)
+    for (const auto& m : member[c])
+      for (int j = 0; j < n_out; ++j) {
+        const int v = weights[(size_t)j * n_in + m.second];
+        const int lo7 = split ? (int)pmod64(v + 64, 128) - 64 : v;
+        const size_t at = (c / 4) * parts * 1024 + ((c % 4) * 16 + (size_t)j) * 16 + (size_t)m.first;
+        w[at] = (int8_t)lo7;
+        if (split) w[at + 1024] = (int8_t)((v - lo7) / 128);
+      }
+  const size_t at = tab.size();
+  tab.resize(at + w.size() / 4);
+  memcpy(&tab[at], w.data(), w.size());
+  b.t_choff = (int32_t)tab.size();
+  for (int c = 0; c < 4 * b.steps; ++c) tab.push_back(c < (int)chunks.size() ? (int32_t)chunks[(size_t)c] : (int32_t)chunks[0]);
+  b.t_bias = (int32_t)tab.size();
+  for (int j = 0; j < 16; ++j) {
+    int64_t sum = 0;
+    for (int i = 0; j < n_out && i < n_in; ++i) sum += weights[(size_t)j * n_in + i];
+    tab.push_back((int32_t)((j < n_out && bias ? bias[j] : 0) + 128 + 128 * sum));
+  }
+  int64_t blocks = 1, terms = 0;
+  for (int k = 0; k < a.rr; ++k) {
+    const int e = k == last ? kLinBoxX : k == kj ? kLinBoxY : 1;
+    b.nb[k] = (a.R[k] + e - 1) / e;
+    b.mg_nb[k] = magic((uint32_t)b.nb[k]);
+    blocks *= b.nb[k];
+    terms += (int64_t)b.nb[k] * (a.ra + a.ro);
+  }
+  if (blocks >= (1LL << 24) || terms > kLinCoordTable) return;
+  for (int k = 0; k < a.rr; ++k) {
+    const int64_t e = k == last ? kLinBoxX : k == kj ? kLinBoxY : 1;
+    b.t_org[k] = (int32_t)tab.size();
+    for (int64_t i = 0; i < b.nb[k]; ++i) {
+      for (int d = 0; d < a.ra; ++d) tab.push_back((int32_t)pmod64((int64_t)Ps[d][k] * (i * e), a.S[d]));
+      for (int d = 0; d < a.ro; ++d) tab.push_back((int32_t)((int64_t)a.Po[d][k] * (i * e) % a.So[d]));
+    }
+  }
+  for (int d = 0; d < a.ra; ++d) {
+    b.org0[d] = (int32_t)pmod64((int64_t)a.o[d] + b.dlo[d], a.S[d]);
+    b.mg_bn[d] = magic((uint32_t)b.bn[d]);
+  }
+  for (int d = 0; d < a.ro; ++d) {
+    b.oorg0[d] = a.oo[d];
+    auto near = [&](int k) { return (int64_t)a.Po[d][k] * 2 > a.So[d] ? a.Po[d][k] - a.So[d] : a.Po[d][k]; };
+    b.Pl[d] = near(last);
+    b.Pj[d] = kj >= 0 ? near(kj) : 0;
+    // a point's base from its block's corner: one addition or subtraction wraps it
+    if (std::abs((int64_t)b.Pl[d]) * (kLinBoxX - 1) + std::abs((int64_t)b.Pj[d]) * (kLinBoxY - 1) > a.So[d]) return;
+  }
+  b.mg_nch = magic((uint32_t)b.nch);
+  b.align = 16;
+  for (int64_t v : chunks)
+    while (v % b.align) b.align /= 2;
+  while (b.lstep % b.align || b.jstep % b.align) b.align /= 2;
+  b.split = split ? 1 : 0;
+  b.use = 1;
+}
+
 }  // namespace
 
 extern "C" {
@@ -290,6 +546,7 @@ aol_status aol_linear_plan_create(const aol_tiler* in, const aol_tiler* out, con
   a.ro = out->array_rank;
   a.n_pairs = n_pairs;
   a.n_out = n_out;
+  a.nout_pad = NOUT;
   std::vector<int32_t> ioff, ifd, ooff, ofd;
   side(in, n_in, n_pad, a.S, a.st, a.o, a.P, a.lo, a.hi, a.inc, ioff, ifd);
   side(out, n_out, NOUT, a.So, a.sto, a.oo, a.Po, a.olo, a.ohi, a.oinc, ooff, ofd);
@@ -331,7 +588,8 @@ aol_status aol_linear_plan_create(const aol_tiler* in, const aol_tiler* out, con
   tab.insert(tab.end(), ooff.begin(), ooff.end());
   a.t_ofd = (int32_t)tab.size();
   tab.insert(tab.end(), ofd.begin(), ofd.end());
-  {
+  plan_pack(a, in, out, weights, bias, n_in, n_out, p->pack);
+  if (!p->pack.inst) {
     std::vector<int32_t> eg, og;
     plan_stage(a, NOUT, ioff, ooff, n_in, n_out, p->stage, eg, og);
     if (p->stage.ppt) {
@@ -390,6 +648,16 @@ aol_status aol_linear_plan_create(const aol_tiler* in, const aol_tiler* out, con
       }
     }
   }
+  if (!p->pack.inst && !p->stage.ppt) {
+    plan_box(a, in, weights, bias, n_in, n_out, p->box, tab);
+    if (p->box.use) {
+      const hipError_t e = linear_box_prepare(p->box);
+      if (e != hipSuccess) {
+        delete p;
+        return hip_fail(e, "linear kernel attributes");
+      }
+    }
+  }
   if ((st = p->d_tab.upload(tab.data(), tab.size() * sizeof(int32_t)))) {
     delete p;
     return st;
@@ -407,7 +675,10 @@ aol_status aol_linear_run(aol_linear_plan* plan, const uint8_t* d_in, uint8_t* d
   a.out = d_out;
   // the staged form loads and stores whole 16-byte chunks: both arrays 16-byte aligned
   const bool staged = plan->stage.ppt > 0 && (((uintptr_t)d_in | (uintptr_t)d_out) & 15) == 0;
-  hipError_t e = staged ? linear_staged_launch(plan->nout, a, plan->stage, stream) : linear_launch(plan->nout, a, stream);
+  hipError_t e = plan->pack.inst ? linear_pack_launch(a, plan->pack, stream)
+                 : staged        ? linear_staged_launch(plan->nout, a, plan->stage, stream)
+                 : plan->box.use ? linear_box_launch(a, plan->box, stream)
+                                 : linear_launch(plan->nout, a, stream);
   if (e != hipSuccess) return hip_fail(e, "linear task launch");
   return ok();
 }

@@ -32,7 +32,7 @@ struct LinearArgs {
   int32_t Po[kLinRank][kLinRank];
   int32_t olo[kLinRank], ohi[kLinRank];
   int32_t n_pairs;                      // input pattern elements, in pairs (an odd count is padded)
-  int32_t n_out;                        // output pattern elements
+  int32_t n_out, nout_pad;              // output pattern elements, and as the tables hold them
   // Device table (int32), uniform reads:
   //   ioff[2 * n_pairs]            flat offset of input element i (pattern inside the array)
   //   ifd[ra][2 * n_pairs]         fitting offset of element i along each dim, reduced mod S
@@ -88,6 +88,66 @@ struct LinearStage {
   uint32_t mg_R[kLinRank];  // floor(2^32 / R[k]) + 1, and of chunks at [last]
 };
 
+// Matrix-core form, for patterns of many elements: a workgroup takes a block
+// of kLinBoxX points of the last repetition dim by kLinBoxY of another (every
+// other index fixed), loads the box of input elements their patterns read into
+// LDS (as x - 128, wrapped while loading) and runs the elementary task as a
+// product on the matrix cores: 16 outputs x K pattern elements x 16 points.
+// The pattern's elements are covered by 16-byte chunks of the box (K may run
+// in any order, and a byte of a chunk that is no element has weight zero).
+constexpr int kLinBoxX = 32, kLinBoxY = 8;
+constexpr int kLinBoxLds = 64 * 1024;  // LDS bytes of a workgroup at most
+constexpr int kLinBoxSteps = 32;       // K-steps (of four chunks) at most
+
+struct LinearBox {
+  int32_t use;                        // 0: not available
+  int32_t split;                      // weights as lo + 128 * hi
+  int32_t k_loop;                     // the other dim of a block (-1: none)
+  int32_t nb[kLinRank];               // blocks along each repetition dim
+  int32_t bn[kLinRank], dlo[kLinRank];  // box extent, and origin relative to the corner point's base (mod S)
+  int32_t rows, pitch, nch;           // box rows (all dims but the last), bytes and chunks between them
+  uint32_t mg_nb[kLinRank], mg_bn[kLinRank], mg_nch;  // floor(2^32 / n) + 1 of nb, bn and nch
+  int32_t lstep, jstep;               // box bytes between points of the last dim / the other dim
+  int32_t steps;                      // K-steps
+  int32_t lds_roff, lds_box, lds_bytes;  // the chunk offsets sit at 0
+  // table offsets (int32 entries): weights in lane order, chunk offsets
+  // (4 * steps, relative to a point's position), bias + 128 + 128 * sum(W)
+  int32_t t_w, t_choff, t_bias;
+  // per repetition dim k and block b along it, at t_org[k] + b * (ra + ro): the
+  // terms of the box origin (input dims) and of the corner point's output base
+  // (output dims), reduced mod the shapes; the constant parts in org0, oorg0
+  int32_t t_org[kLinRank], org0[kLinRank], oorg0[kLinRank];
+  int32_t Pl[kLinRank], Pj[kLinRank];  // output paving along the last dim / the other dim, signed, nearest zero
+  int32_t align;                      // largest power of two (up to 16) dividing every chunk's position
+};
+
+// Packed form: consecutive points of a run read and write runs of consecutive
+// bytes. Where no point's pattern wraps and the flat positions are linear in
+// the repetition index, a run is the last repetition dim, or it and the ones
+// before it where they continue it in both arrays. The input is NI streams of
+// SI bytes per point, the output NO streams of SO bytes; slot q of a point is
+// byte q mod S of stream q / S. Instances: kLinPacks.
+constexpr int kLinPackSlots = 3;   // bytes in and out per point
+constexpr int kLinPackPoints = 16;  // points per thread
+struct LinearPack {
+  int32_t inst;                         // index into kLinPacks + 1 (0: not available)
+  int32_t len, groups;                  // points per run, workgroups per run
+  int32_t n_outer;                      // repetition dims outside the run, slowest first
+  int32_t R[kLinRank];                  // their extents
+  uint32_t mg_R[kLinRank], mg_groups;   // floor(2^32 / n) + 1
+  int64_t fi[kLinRank], fo[kLinRank];   // their flat strides
+  int64_t bi[kLinPackSlots], bo[kLinPackSlots];  // flat position of the first point's byte, per stream
+  int32_t w[kLinPackSlots][kLinPackSlots];       // weight of input slot i for output slot j, [j][i]
+  int32_t bias[kLinPackSlots];          // bias + 128
+};
+struct LinearPackShape {
+  int si, ni, so, no;
+};
+constexpr LinearPackShape kLinPacks[] = {{3, 1, 1, 3}, {1, 3, 3, 1}};
+
+hipError_t linear_pack_launch(const LinearArgs& a, const LinearPack& p, hipStream_t stream);
+hipError_t linear_box_launch(const LinearArgs& a, const LinearBox& b, hipStream_t stream);
+hipError_t linear_box_prepare(const LinearBox& b);
 hipError_t linear_launch(int nout, const LinearArgs& a, hipStream_t stream);
 hipError_t linear_staged_launch(int nout, const LinearArgs& a, const LinearStage& st, hipStream_t stream);
 
