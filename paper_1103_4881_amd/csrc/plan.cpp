@@ -477,6 +477,7 @@ static aol_status plan_build_band(aol_plan* pl, int xreps, int seg) {
     }
   }
   pl->cus = cus;
+  pl->pick.store(0, std::memory_order_relaxed);
   pl->use_band = true;
   return AOL_OK;
 }
@@ -629,31 +630,58 @@ static int64_t strip_wgs(const aol_plan* plan, int form, int segb) {
   return wgs;
 }
 
-// Form and vertical blocks per segment of a launch over n frames (I420
-// 1920x1080 at 3/8 unless said):
+// Form and vertical blocks per segment of a launch over n frames:
 //  * eight waves, segments of about 512 input lines (256 of 16-bit elements),
 //    where that makes four rounds of resident workgroups: a wider workgroup
-//    reads fewer lines twice at its sides (300 frames: u8 0.232 against 0.239
-//    ms, bf16 0.480 against 0.507);
-//  * else four waves, the segments halved down to four blocks until the
-//    workgroups make one round (24 frames of 3840x2160 at 2/3: 18 blocks 0.107
-//    ms, 9 0.112, 4 0.131; 16 of 1280x720 fp16 at 1/2: 4 blocks 14.9 us, 2 16.5:
-//    every workgroup pays its set-up), and down to one block while there are
-//    fewer workgroups than compute units (one frame: the kernel takes 8.5 us
-//    with one block, 10.3 with two, 13.1 with four).
+//    reads fewer lines twice at its sides (300 I420 frames of 1920x1080 at 3/8:
+//    u8 0.232 against 0.239 ms, bf16 0.481 against 0.507);
+//  * else four waves; segments of 288 lines where that makes four rounds (74
+//    frames of 2912x2185 at 1/2: 128 lines 0.208 ms, 288 0.209, 512 0.217, 1536
+//    0.239; 200 of 1920x1080 at 2/3: 144 lines 0.252, 288 0.218, 480 0.211);
+//  * else the segments whose rounds are estimated shortest. A workgroup takes
+//    its steps and about two for its set-up; resident ones share their compute
+//    unit, but one or two alone leave it half idle, so a few workgroups over a
+//    whole round cost nearly another (20 frames of 3840x2160 at 1/2: 480
+//    workgroups 51 us, 800, where a round is 768, 61), and a single frame wants
+//    the shortest segments (one I420 1920x1080 frame: the kernel takes 8.5 us
+//    with one block, 10.3 with two, 13.1 with four). Up to 256 lines for
+//    16-bit elements: bound by memory, they run better with all workgroups in
+//    one region (19 I420 frames of 2160x1217 at 2/3: 6 blocks 77 us, 32 87).
 static int strip_form(const aol_plan* plan, int n_frames, const aol_plan::BandSched* sc, int* segb) {
   const StripTables& T = plan->strips;
-  int sb = std::max(1, sc->seg * T.p_v / 16);
-  const int wide = std::max(1, plan->elem == kU8 ? sb : sb / 2);
-  if (T.wnb[kStripWide] && plan->bseg == 0 && strip_wgs(plan, kStripWide, wide) * n_frames >= 4 * 2 * (int64_t)plan->cus) {
+  const int p = T.p_v, q = T.host.per_steps;  // a block takes q / p steps
+  if (plan->bseg > 0) {
+    *segb = std::max(1, sc->seg * p / 16);
+    return kStripUsual;
+  }
+  auto blocks = [&](int lines) { return std::min(64, std::max(1, lines * p / (16 * q))); };
+  const int wide = blocks(plan->elem == kU8 ? 512 : 256);
+  if (T.wnb[kStripWide] && strip_wgs(plan, kStripWide, wide) * n_frames >= 4 * 2 * (int64_t)plan->cus) {
     *segb = wide;
     return kStripWide;
   }
-  if (plan->bseg == 0) {
-    while (sb > 4 && strip_wgs(plan, kStripUsual, sb) * n_frames < 4 * (int64_t)plan->cus) sb = std::max(4, sb / 2);
-    while (sb > 1 && strip_wgs(plan, kStripUsual, sb) * n_frames < plan->cus) --sb;
+  const int64_t slots = (int64_t)plan->cus * T.resident;
+  *segb = blocks(288);
+  if (strip_wgs(plan, kStripUsual, *segb) * n_frames >= 4 * slots) return kStripUsual;
+  int64_t best = INT64_MAX;
+  for (int sb : {1, 2, 3, 4, 6, 8, 9, 12, 16, 18, 24, 32, 48, 64}) {
+    if (sb > 1 && plan->elem != kU8 && sb > blocks(256)) break;
+    int64_t wgs = 0, steps = 0;
+    for (int i = 0; i < plan->n_planes; ++i) {
+      StripStream S = plan->sstreams[i];
+      strip_set_segments(S, T.wnb[kStripUsual], sb);
+      const int64_t w = (int64_t)S.wgx * S.nseg * n_frames;
+      wgs += w;
+      steps += w * (S.segb * q / p + 4);
+    }
+    const int64_t rest = wgs % slots;
+    const int64_t rounds = wgs / slots * T.resident + (rest ? std::max<int64_t>(2, (rest + plan->cus - 1) / plan->cus) : 0);
+    const int64_t t = steps * rounds / wgs;
+    if (t < best) {
+      best = t;
+      *segb = sb;
+    }
   }
-  *segb = sb;
   return kStripUsual;
 }
 
@@ -663,13 +691,19 @@ static aol_status run_strips(aol_plan* plan, int32_t n_frames, const void* const
   memset(&L, 0, sizeof L);
   L.n_planes = plan->n_planes;
   L.filter = plan->strips.host;
-  int segb = 1;
-  const int form = strip_form(plan, n_frames, band_pick_sched(plan, n_frames), &segb);
-  int64_t wgs = 0, bytes = 0;
+  // The rule depends on the plan and n_frames alone; its last answer is kept.
+  uint64_t pick = plan->pick.load(std::memory_order_relaxed);
+  if (pick >> 32 != (uint64_t)n_frames) {
+    int sb = 1;
+    const int f = strip_form(plan, n_frames, band_pick_sched(plan, n_frames), &sb);
+    pick = (uint64_t)n_frames << 32 | (uint64_t)f << 16 | (uint64_t)sb;
+    plan->pick.store(pick, std::memory_order_relaxed);
+  }
+  const int form = (int)(pick >> 16 & 0xFFFF), segb = (int)(pick & 0xFFFF);
+  int64_t wgs = 0;
   for (int i = 0; i < plan->n_planes; ++i) {
     StripStream& S = L.st[i];
     S = plan->sstreams[i];
-    bytes += (int64_t)n_frames * ((int64_t)S.h * S.w * (plan->elem == kU8 ? 1 : 2) + (int64_t)S.mh * S.mw * (plan->elem == kU8 ? 1 : 4));
     strip_set_segments(S, plan->strips.wnb[form], segb);
     S.wg_base = (int32_t)wgs;
     wgs += (int64_t)S.wgx * S.nseg;
@@ -683,11 +717,10 @@ static aol_status run_strips(aol_plan* plan, int32_t n_frames, const void* const
   L.wgs_per_frame = (int32_t)wgs;
   L.mg_wgs = strip_magic(L.wgs_per_frame);
   // Workgroups that share lines (neighbours in a row, the segments of a
-  // column) on one XCD, for its L2; but a launch well beyond the memory-side
-  // cache (256 MiB) runs all XCDs through the same frames (24 frames of
-  // 3840x2160, 431 MB: 0.107 against 0.111 ms; 300 of 1920x1080, 1065 MB:
-  // 0.239 against 0.232).
-  L.by_xcd = total <= kStripMaxGrid && bytes < (512LL << 20) ? 1 : 0;
+  // column) on one XCD, for its L2 (200 frames of 1920x1080 at 2/3: 0.218
+  // against 0.229 ms); the wide form's share fewer, and it runs better with all
+  // XCDs in the same frames (300 frames at 3/8: 0.232 against 0.239).
+  L.by_xcd = form == kStripUsual && total <= kStripMaxGrid ? 1 : 0;
   for (int first = 0; first < total; first += kStripMaxGrid) {
     L.first = first;
     hipError_t e = strip_launch(plan->elem, plan->strips.cls, form, plan->sedges, L,
@@ -815,11 +848,13 @@ const char* aol_plan_schedule(aol_plan* plan, int32_t n_frames) {
   if (plan->use_band) {
     const aol_plan::BandSched* sc = band_pick_sched(plan, std::max(1, (int)n_frames));
     const int64_t items = (int64_t)sc->units * std::max(1, (int)n_frames);
+    int segb = 0;
+    const int form = strip_form(plan, std::max(1, (int)n_frames), sc, &segb);
     snprintf(buf, sizeof buf,
              "{\"kernel\": \"band\", \"seg\": %d, \"units_per_frame\": %d, \"items\": %lld, \"grid\": %lld, "
-             "\"slots\": %d, \"kmax\": %d, \"split\": %d, \"lds\": %zu}",
+             "\"slots\": %d, \"kmax\": %d, \"split\": %d, \"lds\": %zu, \"form\": %d, \"seg_blocks\": %d}",
              sc->seg, sc->units, (long long)items, (long long)std::min<int64_t>(items, plan->bgrid), plan->bslots,
-             plan->fbands.kmax, plan->fbands.split ? 1 : 0, plan->blds);
+             plan->fbands.kmax, plan->fbands.split ? 1 : 0, plan->blds, form, segb);
   } else {
     snprintf(buf, sizeof buf, "{\"kernel\": \"tiled\", \"tile\": [%d, %d], \"lds\": %zu}", plan->trx, plan->try_,
              plan->lds);

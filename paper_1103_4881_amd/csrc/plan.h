@@ -1,5 +1,6 @@
 // The downscale plan object (shared by the fused and unfused entry points).
 #pragma once
+#include <atomic>
 #include <string>
 #include <vector>
 
@@ -70,6 +71,7 @@ struct aol_plan {
   StripStream sstreams[kMaxPlanes];
   bool sedges = false;  // some plane's lines are not whole 16-byte chunks
   int cus = 0;  // compute units of the device
+  std::atomic<uint64_t> pick{0};  // n_frames << 32 | form << 16 | blocks per segment of the last launch
   std::string sched_json;  // text returned by aol_plan_schedule
   bool split = false;
   DeviceBuf d_hb, d_vb, d_hfrag, d_vfrag;

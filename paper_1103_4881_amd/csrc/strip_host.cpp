@@ -142,6 +142,7 @@ aol_status build_strip_tables(const FilterHost& hf, const FilterHost& vf, int el
   out.col0 = hb.s_min - hb.delta;
   out.line0 = vb.s_min;
   out.p_v = p;
+  out.resident = c == 0 && !split ? 4 : 3;
   out.cls = 2 * c + (split ? 1 : 0);
   return AOL_OK;
 }

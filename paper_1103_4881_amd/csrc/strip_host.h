@@ -16,6 +16,7 @@ struct StripTables {
   int wnb[kStripForms] = {0, 0};  // strips per workgroup at most, by form (0: no instance)
   int col0 = 0, line0 = 0;
   int p_v = 1;
+  int resident = 3;   // workgroups of the usual form resident on a compute unit (registers)
   size_t lds[kStripForms] = {0, 0};  // bytes of a workgroup, by form
   StripFilter host{};
   DeviceBuf d_filter, d_hfrag, d_vfrag, d_bias;
