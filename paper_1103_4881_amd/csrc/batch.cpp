@@ -1,7 +1,8 @@
 // Batched downscaling of many video streams of uneven sizes, ratios and tap
-// counts in one persistent launch per step (one frame of every stream), with
-// a device pointer table so the launch can be captured once in a hipGraph,
-// and an autotuner for the band schedule.
+// counts in one launch per step (one frame of every stream; a second one for
+// the streams whose lines are not whole 16-byte chunks), with a device pointer
+// table so the launch can be captured once in a hipGraph, and an autotuner for
+// the schedule.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -17,6 +18,7 @@
 #include "aolmi.h"
 #include "band_host.h"
 #include "common.h"
+#include "strip_host.h"
 
 using namespace aol;
 
@@ -77,6 +79,20 @@ struct aol_batch_plan {
     DeviceBuf d_units, d_order, d_first;  // unit_capacity, unit_capacity, unit_capacity + 1 entries
   };
   Part parts[2];
+  // The strip kernel (where it has an instance for every stream; the parts
+  // above serve the others): one launch of the streams whose lines are whole
+  // 16-byte chunks and one of the rest.
+  bool strips = false;
+  std::vector<StripTables> tables;    // one per filter group
+  std::vector<StripStream> sstreams;
+  struct StripPart {
+    std::vector<int> ids;
+    size_t unit_capacity = 0;
+    int units = 0;                    // of the current schedule
+    size_t lds = 0;
+    DeviceBuf d_units;
+  };
+  StripPart sparts[2];                // whole chunks, edges
   // Both parts in one launch (k_band_dual): each on its own share of the
   // workgroups, in proportion to its estimated cost.
   bool dual = false;
@@ -211,6 +227,122 @@ static aol_status batch_place_part(aol_batch_plan::Part& P, int grid) {
   return AOL_OK;
 }
 
+// Device tables of the strip kernel; bp->strips stays false when a stream is
+// beyond its instances.
+static aol_status batch_strips(aol_batch_plan* bp, const std::vector<int>& rep) {
+  bp->tables.resize(rep.size());
+  for (size_t g = 0; g < rep.size(); ++g) {
+    if (aol_status st = build_strip_tables(bp->hf[rep[g]], bp->vf[rep[g]], bp->elem, bp->tables[g])) return st;
+    if (bp->tables[g].cls < 0) return AOL_OK;
+  }
+  bp->sstreams.resize(bp->n);
+  for (int i = 0; i < bp->n; ++i) {
+    const StripTables& T = bp->tables[bp->filt[i]];
+    const aol_stream_desc& d = bp->desc[i];
+    StripStream& S = bp->sstreams[i];
+    if (!build_strip_stream(T, d.height, d.width, d.in_pitch, d.out_pitch, S)) return AOL_OK;
+    aol_batch_plan::StripPart& P = bp->sparts[strip_edges(T, S) ? 1 : 0];
+    P.ids.push_back(i);
+    P.lds = std::max(P.lds, T.lds[kStripUsual]);
+    const int wnb = T.wnb[kStripUsual];
+    P.unit_capacity += (size_t)((S.nbh + wnb - 1) / wnb) * (size_t)S.nbv;
+  }
+  for (int e = 0; e < 2; ++e) {
+    aol_batch_plan::StripPart& P = bp->sparts[e];
+    if (P.ids.empty()) continue;
+    if (P.unit_capacity > (size_t)INT_MAX / 512) return AOL_OK;  // (a grid holds fewer than 2^32 threads)
+    if (aol_status st = P.d_units.alloc(sizeof(StripUnit) * P.unit_capacity)) return st;
+    hipError_t h = strip_batch_prepare(bp->elem, e == 1, P.lds);
+    if (h != hipSuccess) return hip_fail(h, "strip kernel attributes");
+  }
+  if (aol_status st = bp->d_streams.upload(bp->sstreams.data(), sizeof(StripStream) * bp->sstreams.size())) return st;
+  bp->strips = true;
+  return AOL_OK;
+}
+
+// Units of a schedule: rows of workgroups (one segment of one stream), the
+// heaviest streams first, each to the XCD with the least work so far. The
+// device hands consecutive workgroups to its 8 XCDs in turn, so the lists are
+// interleaved: neighbours in a row share the lines at their sides through one
+// L2, and the light streams fill the last round. (64 uint8 streams of 320x240
+// to 1920x1080, 237 MB: 68 us, with the workgroups of a row on different XCDs
+// 72; where the frames stay in the memory-side cache, 58 against 64.)
+//
+// Segments of 240 input lines (a schedule may name others), shorter ones where
+// they make less than two workgroups per compute unit, down to one block where
+// they make less than one (64 streams: 96 lines 74 us, 144 73, 240 66, 288 70;
+// 10 streams: 64 lines 19.9 us, 96 16.8, 144 18.0, 240 21.7; 5 streams: 32
+// lines 10.0 us, 48 9.7, 96 10.5, 240 15.9).
+static aol_status batch_place_strips(aol_batch_plan* bp, const Schedule& sc) {
+  int dev = 0, cus = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
+  if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
+    return hip_fail(e, "hipDeviceGetAttribute");
+  std::vector<StripStream> streams = bp->sstreams;
+  auto segments = [&](const aol_batch_plan::StripPart& P, int lines) {
+    int64_t units = 0;
+    for (int i : P.ids) {
+      const StripTables& T = bp->tables[bp->filt[i]];
+      const int p = T.p_v, q = T.host.per_steps, c = bp->cls[i];  // a block takes q / p steps
+      const int seg = c < (int)sc.class_seg.size() && sc.class_seg[c] > 0 ? sc.class_seg[c] : sc.seg;
+      strip_set_segments(streams[i], T.wnb[kStripUsual],
+                         (int)std::max<int64_t>(1, seg > 0 ? (int64_t)seg * p / 16 : lines * p / (16 * q)));
+      units += (int64_t)streams[i].wgx * streams[i].nseg;
+    }
+    return units;
+  };
+  for (aol_batch_plan::StripPart& P : bp->sparts) {
+    if (P.ids.empty()) continue;
+    for (int lines : {240, 192, 144, 96, 64, 48, 32, 16})
+      if (segments(P, lines) >= (lines > 96 ? 2 * cus : cus)) break;
+    // cost of a stream's units: steps (and about four for a workgroup's set-up) by columns
+    auto cost = [&](int i, int blocks, int strips) {
+      const StripFilter& F = bp->tables[bp->filt[i]].host;
+      const int64_t steps = (int64_t)blocks * F.per_steps / bp->tables[bp->filt[i]].p_v + 4;
+      return steps * ((int64_t)strips * F.per_chunks / F.nblk_h + 1);
+    };
+    std::vector<int> order = P.ids;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+      return cost(a, streams[a].segb, streams[a].wnb) > cost(b, streams[b].segb, streams[b].wnb);
+    });
+    constexpr int kXcds = 8;
+    std::vector<StripUnit> lists[kXcds];
+    int64_t load[kXcds] = {0};
+    size_t total = 0;
+    for (int i : order) {
+      const StripStream& S = streams[i];
+      const StripTables& T = bp->tables[bp->filt[i]];
+      for (int s = 0; s < S.nseg; ++s) {
+        const int x = (int)(std::min_element(load, load + kXcds) - load);
+        for (int w = 0; w < S.wgx; ++w) {
+          StripUnit U;
+          memset(&U, 0, sizeof U);
+          U.filter = (const StripFilter*)T.d_filter.ptr;
+          U.cls = T.cls;
+          U.stream = i;
+          U.wb0 = w * S.wnb;
+          U.wnb = std::min(S.wnb, S.nbh - U.wb0);
+          U.B0 = s * S.segb;
+          U.B1 = std::min(S.nbv, U.B0 + S.segb);
+          lists[x].push_back(U);
+          load[x] += cost(i, U.B1 - U.B0, U.wnb);
+          ++total;
+        }
+      }
+    }
+    if (total > P.unit_capacity) return fail(AOL_ERR_INVALID, "unit capacity exceeded");
+    std::vector<StripUnit> units;
+    for (size_t k = 0; units.size() < total; ++k)
+      for (const std::vector<StripUnit>& l : lists)
+        if (k < l.size()) units.push_back(l[k]);
+    if ((e = hipMemcpy(P.d_units.ptr, units.data(), sizeof(StripUnit) * total, hipMemcpyHostToDevice)) != hipSuccess)
+      return hip_fail(e, "hipMemcpy");
+    P.units = (int)total;
+  }
+  return AOL_OK;
+}
+
 static aol_status batch_build(aol_batch_plan* bp, const Schedule& sc) {
   // Launches of this plan still in flight on any stream read the tables
   // rewritten below (plain copies do not wait for non-blocking streams).
@@ -226,9 +358,18 @@ static aol_status batch_build(aol_batch_plan* bp, const Schedule& sc) {
   }
   aol_batch_plan::Part &A = bp->parts[0], &B = bp->parts[1];
   const int kmax = std::max(A.kmax, B.kmax);
-  bp->dual = bp->elem == kU8 && !A.ids.empty() && !B.ids.empty() && !A.gather && !B.gather &&
+  bp->dual = !bp->strips && bp->elem == kU8 && !A.ids.empty() && !B.ids.empty() && !A.gather && !B.gather &&
              band_dual_supported(A.slots, B.slots, kmax);
-  if (bp->dual) {
+  if (bp->strips) {
+    if (aol_status st = batch_place_strips(bp, sc)) return st;
+    for (const aol_batch_plan::StripPart& P : bp->sparts) {
+      if (P.ids.empty()) continue;
+      units += P.units;
+      grid = std::max(grid, P.units);
+      lds = std::max(lds, (int)P.lds);
+      ++launches;
+    }
+  } else if (bp->dual) {
     // one launch: the device's resident workgroups split between the parts
     // in proportion to their estimated costs
     bp->dual_lds = std::max(A.lds, B.lds);
@@ -264,8 +405,11 @@ static aol_status batch_build(aol_batch_plan* bp, const Schedule& sc) {
       ++launches;
     }
   }
-  hipError_t e = hipMemcpy(bp->d_streams.ptr, streams.data(), sizeof(BandStream) * streams.size(), hipMemcpyHostToDevice);
-  if (e != hipSuccess) return hip_fail(e, "hipMemcpy");
+  if (!bp->strips) {
+    hipError_t e =
+        hipMemcpy(bp->d_streams.ptr, streams.data(), sizeof(BandStream) * streams.size(), hipMemcpyHostToDevice);
+    if (e != hipSuccess) return hip_fail(e, "hipMemcpy");
+  }
   bp->streams = std::move(streams);
   bp->sched = sc;
   char buf[240];
@@ -296,6 +440,19 @@ static BandLaunch part_launch(const aol_batch_plan* bp, const aol_batch_plan::Pa
 }
 
 static aol_status batch_launch(aol_batch_plan* bp, hipStream_t stream, const void* table = nullptr) {
+  if (bp->strips) {
+    for (int e = 0; e < 2; ++e) {
+      const aol_batch_plan::StripPart& P = bp->sparts[e];
+      if (P.ids.empty()) continue;
+      StripBatch L;
+      L.streams = (const StripStream*)bp->d_streams.ptr;
+      L.units = (const StripUnit*)P.d_units.ptr;
+      L.ptr_table = (void* const*)(table ? table : bp->d_table.ptr);
+      hipError_t h = strip_batch_launch(bp->elem, e == 1, L, P.units, P.lds, stream);
+      if (h != hipSuccess) return hip_fail(h, "batch kernel launch");
+    }
+    return AOL_OK;
+  }
   if (bp->dual) {
     const aol_batch_plan::Part &A = bp->parts[0], &B = bp->parts[1];
     hipError_t e = band_dual_launch(A.slots, B.slots, std::max(A.kmax, B.kmax), part_launch(bp, A, table), A.grid,
@@ -500,8 +657,8 @@ aol_status aol_batch_plan_create(int32_t n_streams, const aol_stream_desc* strea
     bp->cache_path = tune_cache;
     cache_lookup(bp->cache_path, bp->key, &sc);
   }
+  st = batch_strips(bp, rep);
   // capacity: the most units any schedule can make (bands and segments of 16 repetitions)
-  st = AOL_OK;
   for (aol_batch_plan::Part& P : bp->parts) {
     for (int i : P.ids) {
       const int64_t rx = (bp->desc[i].width + bp->hf[i].q - 1) / bp->hf[i].q;
@@ -512,12 +669,12 @@ aol_status aol_batch_plan_create(int32_t n_streams, const aol_stream_desc* strea
       delete bp;
       return fail(AOL_ERR_UNSUPPORTED, "too many units");
     }
-    if (P.ids.empty()) continue;
+    if (P.ids.empty() || bp->strips) continue;
     if (!st) st = P.d_units.alloc(sizeof(BandUnit) * P.unit_capacity);
     if (!st) st = P.d_order.alloc(sizeof(int32_t) * P.unit_capacity);
     if (!st) st = P.d_first.alloc(sizeof(int32_t) * (P.unit_capacity + 1));
   }
-  if (!st) st = bp->d_streams.alloc(sizeof(BandStream) * (size_t)n_streams);
+  if (!st && !bp->strips) st = bp->d_streams.alloc(sizeof(BandStream) * (size_t)n_streams);
   if (!st) st = batch_build(bp, sc);
   if (!st) st = bp->d_table.alloc(sizeof(void*) * 2 * (size_t)n_streams);
   if (st) {
@@ -724,6 +881,7 @@ aol_status aol_autotune(aol_batch_plan* plan, hipStream_t stream) {
   bool go = true;
   for (int budget : budgets)
     for (int seg : segs) {
+      if (plan->strips && budget != budgets[0]) continue;  // the strip kernel has no column band
       Schedule sc;
       sc.seg = seg;
       sc.budget = budget;

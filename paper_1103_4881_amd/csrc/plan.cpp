@@ -466,7 +466,6 @@ static aol_status plan_build_band(aol_plan* pl, int xreps, int seg) {
     for (int i = 0; i < pl->n_planes && pl->strips.cls >= 0; ++i) {
       const aol_plane_desc& d = pl->planes[i];
       if (!build_strip_stream(pl->strips, d.height, d.width, d.in_pitch, d.out_pitch, pl->sstreams[i])) pl->strips.cls = -1;
-      pl->sstreams[i].ptr = i;
       pl->sedges = pl->sedges || strip_edges(pl->strips, pl->sstreams[i]);
     }
     for (int f = 0; f < kStripForms && pl->strips.cls >= 0; ++f) {

@@ -56,7 +56,6 @@ struct alignas(16) StripFilter {
 
 // One plane or video stream.
 struct alignas(16) StripStream {
-  const StripFilter* filter;    // NULL: the launch's
   int64_t in_pitch, out_pitch;  // elements
   int32_t h, w, mh, mw;         // input and output sizes
   int32_t col0, line0;          // input column of chunk 0 and line of step 0 (before the wrap)
@@ -65,25 +64,30 @@ struct alignas(16) StripStream {
   int32_t segb, nseg;           // vertical blocks per segment, segments
   uint32_t mg_wgx;              // floor(2^32 / wgx) + 1
   int32_t wg_base;              // first workgroup of the plane inside a frame
-  int32_t ptr;                  // entry of the pointer table
-  int32_t cls;                  // 2 * class + split
   int32_t tiny;                 // a line is shorter than one 16-byte chunk
-  int32_t pad;
+  int32_t pad[3];
 };
 
-// One workgroup of a batch: a stream, its column of workgroups and its
-// vertical blocks [B0, B1).
-struct StripUnit {
-  int32_t stream, wx, B0, B1;
+// One workgroup of a batch: strips [wb0, wb0 + wnb) and vertical blocks
+// [B0, B1) of a stream.
+struct alignas(16) StripUnit {
+  const StripFilter* filter;
+  int32_t cls;                  // 2 * class + split
+  int32_t stream;               // index of the stream and of its pointers
+  int32_t wb0, wnb, B0, B1;
+};
+
+// One launch of a batch: a workgroup per unit.
+struct StripBatch {
+  const StripStream* streams;
+  const StripUnit* units;
+  void* const* ptr_table;       // [in, out] per stream
 };
 
 struct StripLaunch {
   StripFilter filter;            // a plan's filters, in the launch's arguments: one dependent load less
   StripStream st[kMaxPlanes];    // a plan's planes
-  const StripStream* streams;    // a batch's streams (device), or NULL
-  const StripUnit* units;        // a batch's workgroups (device), or NULL
-  void* const* ptr_table;        // a batch's device pointers [in, out] per stream
-  const void* ptrs[2 * kMaxPlanes];  // a plan's
+  const void* ptrs[2 * kMaxPlanes];  // in, out per plane
   int64_t fstride[2 * kMaxPlanes];   // elements between frames (in, out) per plane
   int32_t n_planes, wgs_per_frame;
   uint32_t mg_wgs;               // floor(2^32 / wgs_per_frame) + 1

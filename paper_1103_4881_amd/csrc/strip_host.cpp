@@ -113,8 +113,6 @@ aol_status build_strip_tables(const FilterHost& hf, const FilterHost& vf, int el
           }
         }
   F.vfrag_bytes = (int32_t)vfr.size();
-  if ((st = out.d_hfrag.upload(hfr.data(), hfr.size()))) return st;
-  if ((st = out.d_vfrag.upload(vfr.data(), vfr.size()))) return st;
   F.lds_x = (int32_t)((vfr.size() + (size_t)vb.nblk * 16 * 4 + 15) / 16 * 16);
   // strips per workgroup: as many as its waves take, within the staged chunks
   // wherever in the period the first one lies
@@ -133,11 +131,25 @@ aol_status build_strip_tables(const FilterHost& hf, const FilterHost& vf, int el
     }
   }
   if (out.wnb[kStripUsual] < 1) return AOL_OK;
-  if ((st = out.d_bias.upload(bias.data(), bias.size() * sizeof(int32_t)))) return st;
-  F.bias = (const int32_t*)out.d_bias.ptr;
-  F.hfrag = out.d_hfrag.ptr;
-  F.vfrag = out.d_vfrag.ptr;
-  if ((st = out.d_filter.upload(&F, sizeof F))) return st;
+  // one allocation and one copy: the filter, then its operands and biases
+  const size_t bias_bytes = bias.size() * sizeof(int32_t);
+  std::vector<uint8_t> mem(sizeof F + hfr.size() + vfr.size() + bias_bytes);
+  if ((st = out.d_filter.alloc(mem.size()))) return st;
+  const uint8_t* dev = (const uint8_t*)out.d_filter.ptr;
+  size_t at = sizeof F;
+  auto place = [&](const void* src, size_t n) {
+    memcpy(&mem[at], src, n);
+    const uint8_t* p = dev + at;
+    at += n;
+    return p;
+  };
+  static_assert(sizeof F % 16 == 0, "operands of whole 16-byte chunks follow");
+  F.hfrag = place(hfr.data(), hfr.size());
+  F.vfrag = place(vfr.data(), vfr.size());
+  F.bias = (const int32_t*)place(bias.data(), bias_bytes);
+  memcpy(&mem[0], &F, sizeof F);
+  hipError_t e = hipMemcpy(out.d_filter.ptr, mem.data(), mem.size(), hipMemcpyHostToDevice);
+  if (e != hipSuccess) return hip_fail(e, "hipMemcpy");
   out.elem = elem;
   out.col0 = hb.s_min - hb.delta;
   out.line0 = vb.s_min;
@@ -166,7 +178,6 @@ bool build_strip_stream(const StripTables& t, int64_t h, int64_t w, int64_t in_p
   S.line0 = t.line0;
   S.nbh = (S.mw + 15) / 16;
   S.nbv = (S.mh + 15) / 16;
-  S.cls = t.cls;
   S.tiny = w * es < 16 ? 1 : 0;
   return true;
 }

@@ -19,7 +19,7 @@ struct StripTables {
   int resident = 3;   // workgroups of the usual form resident on a compute unit (registers)
   size_t lds[kStripForms] = {0, 0};  // bytes of a workgroup, by form
   StripFilter host{};
-  DeviceBuf d_filter, d_hfrag, d_vfrag, d_bias;
+  DeviceBuf d_filter;  // the filter, followed by its operands and biases
 };
 
 // AOL_OK with out.cls = -1 when no instance serves the filters.
@@ -41,6 +41,12 @@ void strip_set_segments(StripStream& S, int wnb, int segb);
 
 // edges: some line of the launch is not whole 16-byte chunks.
 hipError_t strip_prepare(int elem, int cls, int form, bool edges, size_t lds_bytes);
+
+// A batch: units of streams of any filter class; edges: of streams with a line
+// that is not whole 16-byte chunks.
+hipError_t strip_batch_prepare(int elem, bool edges, size_t lds_bytes);
+hipError_t strip_batch_launch(int elem, bool edges, const StripBatch& L, int grid, size_t lds_bytes, hipStream_t stream);
+
 hipError_t strip_launch(int elem, int cls, int form, bool edges, const StripLaunch& L, int grid, size_t lds_bytes,
                         hipStream_t stream);
 
