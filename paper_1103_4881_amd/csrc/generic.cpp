@@ -216,7 +216,6 @@ static aol_status wsum_create(const aol_tiler* in, const aol_tiler* out, const f
   a.k_loop = k_loop;
   a.transpose = (identity && k_loop == a.rr - 1 && k_lane != k_loop) ? 1 : 0;
   for (int d = 0; d < kWsumMaxRank; ++d) {
-    a.P_loop[d] = d < a.ra ? a.P[d][k_loop] : 0;
     a.Po_loop[d] = d < a.ro ? a.Po[d][k_loop] : 0;
   }
   a.nb_lane = (int32_t)((R[k_lane] + 63) / 64);
@@ -235,7 +234,7 @@ static aol_status wsum_create(const aol_tiler* in, const aol_tiler* out, const f
     return fail(AOL_ERR_UNSUPPORTED, "repetition space needs too many workgroups");
   }
 
-  // Staged form: the box of input elements one 64x64 block of points reads,
+  // Staged form: the box of input elements one block of points (64 x 4 * kWsumBoxPoints) reads,
   // when it is small enough for LDS and no pattern spans an array extent.
   {
     bool fit = true;
@@ -264,13 +263,20 @@ static aol_status wsum_create(const aol_tiler* in, const aol_tiler* out, const f
     }
     fit = fit && elems * 4 <= kWsumBoxMaxBytes && p->in_elems * 4 < (1LL << 32);
     if (fit) {
+      // Rows in whole chunks unless they are so short that the padding would
+      // outgrow LDS (a chunk also has to wrap at most once).
+      const int rowlen = a.bn[a.ra - 1];
+      a.box_rows = (int32_t)(elems / rowlen);
+      const int chunks = (rowlen + 3) / 4;
+      a.box_chunks = a.S[a.ra - 1] >= 4 && (int64_t)a.box_rows * chunks * 16 <= kWsumBoxMaxBytes ? chunks : 0;
+      a.mg_chunks = magic(std::max(1, a.box_chunks));
+      if (a.box_chunks) elems = (int64_t)a.box_rows * chunks * 4;
       int64_t bst[kWsumMaxRank] = {0, 0, 0, 0}, s1 = 1;
       for (int d = a.ra - 1; d >= 0; --d) {
         bst[d] = s1;
-        s1 *= a.bn[d];
+        s1 *= d == a.ra - 1 && a.box_chunks ? 4 * chunks : a.bn[d];
       }
       a.box_elems = (int32_t)elems;
-      a.box_rows = (int32_t)(elems / a.bn[a.ra - 1]);
       int64_t ls = 0, js = 0;
       for (int d = 0; d < a.ra; ++d) {
         ls += (int64_t)a.Ps[d][k_lane] * bst[d];
@@ -386,6 +392,18 @@ static aol_status wsum_create(const aol_tiler* in, const aol_tiler* out, const f
         if (a.em) a.cls = a.ctab + a.ctab_cls;
       }
     }
+  }
+  if (!a.use_box) {
+    a.small = 1;
+    for (int d = 0; d < a.ra; ++d) {
+      int64_t most = a.S[d];
+      for (int k = 0; k < a.rr; ++k) most += (a.Ps[d][k] < 0 ? -a.Ps[d][k] : a.Ps[d][k]) * (R[k] + 63);
+      if (most >= INT32_MAX) a.small = 0;
+    }
+    // blocks of 64 x 4 points (fewer blocks than points, so under 2^31)
+    blocks /= a.nb_loop;
+    a.nb_loop = (int32_t)((R[k_loop] + 3) / 4);
+    blocks *= a.nb_loop;
   }
   a.mg_lane = magic(a.nb_lane);
   a.mg_loop = magic(a.nb_loop);

@@ -15,7 +15,6 @@ struct WsumArgs {
   int32_t R[kWsumMaxRank];               // repetition space
   int32_t o[kWsumMaxRank];               // input origin, reduced mod S
   int32_t P[kWsumMaxRank][kWsumMaxRank];  // input paving [dim][rep], reduced mod S
-  int32_t P_loop[kWsumMaxRank];          // P[.][k_loop]
   int32_t lo[kWsumMaxRank], hi[kWsumMaxRank];  // extent of the fitting offsets along each dim
   int32_t npat;
   int32_t off[kMaxPat];                  // flat offset of each pattern element (pattern inside the array)
@@ -28,12 +27,13 @@ struct WsumArgs {
   int32_t Po_loop[kWsumMaxRank];
   int64_t ostr_rep[kWsumMaxRank];        // identity output: stride of each repetition dim
   int32_t k_lane, k_loop;                // repetition dims along lanes / along each thread's loop
-  int32_t nb_lane, nb_loop;              // 64-wide blocks along k_lane / k_loop
+  int32_t small;                         // the points' unwrapped base indices, from Ps, fit 32 bits
+  int32_t nb_lane, nb_loop;              // blocks along k_lane (64 wide) / k_loop
   uint32_t mg_lane, mg_loop, mg_R[kWsumMaxRank];  // floor(2^32 / divisor) + 1 of nb_lane, nb_loop, R
   int32_t other[kWsumMaxRank];
   int32_t n_other;
   int32_t transpose;                     // stage results in LDS and store along k_loop
-  // Staged form: the input box a 64x64 block of points reads (unwrapped
+  // Staged form: the input box a block of points reads (unwrapped
   // coordinates lo + [0, bn) per dim, lo = o + Ps.r_corner + dlo) is loaded
   // into LDS once; pattern element i of point (lane, jj) is then
   // box[lane*lstep + jj*jstep + offl[i]].
@@ -41,6 +41,10 @@ struct WsumArgs {
   int32_t Ps[kWsumMaxRank][kWsumMaxRank];  // paving, signed representative nearest zero
   int32_t dlo[kWsumMaxRank];             // box origin relative to the block's corner point
   int32_t bn[kWsumMaxRank];              // box extent per dim
+  // Rows of the box in 16-byte chunks: chunks per row (the row's pitch in LDS),
+  // or 0 (rows of bn[last] elements, loaded one element a lane).
+  int32_t box_chunks;
+  uint32_t mg_chunks;                    // floor(2^32 / box_chunks) + 1
   int32_t box_rows;                      // product of the extents of all but the last dim
   int32_t box_elems;
   int32_t lstep, jstep;                  // box offset per lane / per loop point

@@ -6,21 +6,28 @@
 // single result to B[(o' + P'.r) mod S']. Here the elementary task is
 // y = sum_i w[i] * pattern[i].
 //
-// Work mapping: a workgroup covers a 64 x 64 block of two repetition
-// dimensions with every other repetition index fixed. Lanes run along the
-// dimension whose paving column walks the input's contiguous axis (the
-// gathers of one pattern element are then adjacent addresses); each thread
-// walks 16 points of the second dimension, updating the wrapped base index
-// incrementally. A pattern that stays inside the array uses constant flat
+// Work mapping: a workgroup covers a block of two repetition dimensions, 64
+// points of the first along its lanes, with every other repetition index
+// fixed. Lanes run along the dimension whose paving column walks the input's
+// contiguous axis (the gathers of one pattern element are then adjacent
+// addresses). A pattern that stays inside the array uses constant flat
 // offsets; one that crosses a border wraps each axis separately. When the
-// output's contiguous dimension is the per-thread one, results go through a
+// output's contiguous dimension is the second one, results go through a
 // transposed LDS tile so that stores are contiguous too.
+//
+// Direct form: one point per thread, four along the second dimension per
+// workgroup. Bound by the latency of a thread's gathers (eight in flight), so
+// points of one thread only lengthen the chain: 10 x 768 x 372 inputs, 25
+// elements: 96 us with 16 points, 29 with four, 20 with one; 57 x 951 x 412, 16
+// elements: 82, 65, 62 us.
 //
 // Staged form (BOX): when the input elements a block of points reads lie in a
 // box small enough for LDS, the workgroup first loads that box (rows along
 // the input's contiguous axis, the modulo wrap applied while loading; the
 // rows' wrapped offsets computed by the lanes in parallel, the box origin
-// from a host table of per-block terms), then every pattern element of
+// from a host table of per-block terms; chunks of 16 bytes, all of a thread's in
+// flight at once: a 64 x 1024 x 1024 array with 25 elements 77 us by single
+// elements, 68 by chunks), then every pattern element of
 // every point is an LDS read at a constant offset from the point's base;
 // each input element comes from HBM once per block. Pattern elements whose
 // offsets differ by a multiple of the loop dimension's step read, at
@@ -40,6 +47,8 @@ namespace aol {
 typedef const __attribute__((address_space(1))) float* gin_t;
 #define AOL_WCONST __attribute__((address_space(4)))
 typedef __attribute__((address_space(1))) float* gout_t;
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));  // in memory, at any element
 
 // Weighted sum of one pattern: the gathers are issued 8 at a time, so that
 // several are in flight instead of one load waiting for the previous one.
@@ -47,15 +56,23 @@ template <class Off>
 __device__ __forceinline__ float wsum_pattern(const WsumArgs& a, Off off) {
   gin_t in = (gin_t)a.in;
   float acc = 0.f;
-  int i = 0;
-  for (; i + 8 <= a.npat; i += 8) {
+  for (int i = 0; i < a.npat; i += 8) {
     float v[8];
+    const int left = a.npat - i;  // uniform
+    if (left >= 8) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = in[off(i + k)];
+      for (int k = 0; k < 8; ++k) v[k] = in[off(i + k)];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) acc = __builtin_fmaf(a.w[i + k], v[k], acc);
+      for (int k = 0; k < 8; ++k) acc = __builtin_fmaf(a.w[i + k], v[k], acc);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 7; ++k)
+        if (k < left) v[k] = in[off(i + k)];
+#pragma unroll
+      for (int k = 0; k < 7; ++k)
+        if (k < left) acc = __builtin_fmaf(a.w[i + k], v[k], acc);
+    }
   }
-  for (; i < a.npat; ++i) acc = __builtin_fmaf(a.w[i], in[off(i)], acc);
   return acc;
 }
 
@@ -115,15 +132,13 @@ __device__ __forceinline__ void wsum_box_classes(const WsumArgs& a, const float*
 }
 
 // PT: points per thread along the loop dimension (a block is 64 x 4*PT
-// points): 16 for the direct form, 8 for the staged form (a smaller box, so
-// more workgroups per compute unit overlap their loads with others' sums).
+// points).
 // EM: the widest class of shared reads (0: one read per pattern element).
-template <bool BOX, int EM>
+template <bool BOX, int EM, int PT>
 __global__ __launch_bounds__(256) void k_wsum(WsumArgs a) {
-  constexpr int PT = BOX ? 8 : 16;
   constexpr int BJ = 4 * PT;  // block extent along the loop dimension
   __shared__ float tile[64][BJ + 1];
-  extern __shared__ float box[];
+  extern __shared__ __attribute__((aligned(16))) float box[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
@@ -167,7 +182,13 @@ __global__ __launch_bounds__(256) void k_wsum(WsumArgs a) {
   for (int d = 0; d < kWsumMaxRank; ++d) {
     base[d] = 0;
     obase[d] = 0;
-    if (!BOX && d < a.ra) {
+    if (!BOX && d < a.ra && a.small) {
+      int v = a.o[d];
+#pragma unroll
+      for (int k = 0; k < kWsumMaxRank; ++k) v += (int)a.Ps[d][k] * (int)r[k];
+      v %= a.S[d];
+      base[d] = v < 0 ? v + a.S[d] : v;
+    } else if (!BOX && d < a.ra) {
       int64_t v = a.o[d];
       for (int k = 0; k < a.rr; ++k) v += (int64_t)a.P[d][k] * r[k];
       base[d] = (int)(v % a.S[d]);
@@ -224,11 +245,10 @@ __global__ __launch_bounds__(256) void k_wsum(WsumArgs a) {
     // the input is under 4 GiB in this form: a uniform base plus a 32-bit byte offset per element
     const __attribute__((address_space(1))) uint8_t* inb = (const __attribute__((address_space(1))) uint8_t*)a.in;
     auto ld = [&](uint32_t elem) { return *(gin_t)(inb + (uint64_t)(elem * 4u)); };
-    // rows along the contiguous axis, eight rows per wave and iteration with
-    // every load issued before the first store (up to 32 loads per lane in
-    // flight).
-    // The wrapped columns of the lane's elements are the same in every row:
-    // computed once. Row coordinates advance by a counter with carries.
+    // Boxes whose rows are too short for chunks: eight rows per wave and
+    // iteration with every load issued before the first store (up to 32 loads
+    // per lane in flight). The wrapped columns of the lane's elements are the
+    // same in every row: computed once.
     const int nt = (rowlen + 63) / 64;  // 64-element pieces of a row
     auto wrap_col = [&](int piece) {  // wrapped column of the lane's element of a 64-element piece
       int c = lo[last] + min(piece * 64 + lane, rowlen - 1);
@@ -258,8 +278,38 @@ __global__ __launch_bounds__(256) void k_wsum(WsumArgs a) {
       roff[q] = gg;
     }
     __syncthreads();
+    constexpr int CB = 8;  // chunks in flight per thread
+    const uint32_t total = (uint32_t)(a.box_rows * a.box_chunks);
+    const bool wraps = lo[last] + 4 * a.box_chunks > a.S[last];  // some chunk of a row
+    for (uint32_t i0 = threadIdx.x; i0 < total; i0 += 256 * CB) {
+      v4f v[CB];
+#pragma unroll
+      for (int k = 0; k < CB; ++k) {
+        const uint32_t idx = min(i0 + 256 * k, total - 1);  // past the last chunk: loaded, not stored
+        if (k > 0 && (i0 & ~255u) + 256 * k >= total) break;  // uniform
+        const uint32_t row = wsum_div(idx, (uint32_t)a.box_chunks, a.mg_chunks);
+        int c = lo[last] + 4 * (int)(idx - row * (uint32_t)a.box_chunks);
+        if (!wraps) {
+          v[k] = *(const __attribute__((address_space(1))) v4f_any*)(inb + (uint64_t)((uint32_t)(roff[row] + c) * 4u));
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            int ce = c + e;
+            if (ce >= a.S[last]) ce -= a.S[last];
+            if (ce >= a.S[last]) ce -= a.S[last];
+            if (ce >= a.S[last]) ce -= a.S[last];
+            v[k][e] = ld((uint32_t)(roff[row] + ce));
+          }
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < CB; ++k) {
+        if (k > 0 && (i0 & ~255u) + 256 * k >= total) break;
+        if (i0 + 256 * k < total) *reinterpret_cast<v4f*>(box + 4 * (i0 + 256 * k)) = v[k];
+      }
+    }
     constexpr int QR = 8;  // rows per wave and iteration
-    for (int row0 = wave * QR; row0 < a.box_rows; row0 += 4 * QR) {
+    for (int row0 = wave * QR; a.box_chunks == 0 && row0 < a.box_rows; row0 += 4 * QR) {
       int g[QR];
 #pragma unroll
       for (int q = 0; q < QR; ++q) g[q] = roff[min(row0 + q, a.box_rows - 1)];  // past the last row: loaded, not stored
@@ -345,11 +395,6 @@ __global__ __launch_bounds__(256) void k_wsum(WsumArgs a) {
     // next point along the loop dimension
 #pragma unroll
     for (int d = 0; d < kWsumMaxRank; ++d) {
-      if (!BOX && d < a.ra) {
-        uint32_t v = (uint32_t)base[d] + (uint32_t)a.P_loop[d];
-        if (v >= (uint32_t)a.S[d]) v -= (uint32_t)a.S[d];
-        base[d] = (int)v;
-      }
       if (!a.out_identity && d < a.ro) {
         uint32_t v = (uint32_t)obase[d] + (uint32_t)a.Po_loop[d];
         if (v >= (uint32_t)a.So[d]) v -= (uint32_t)a.So[d];
@@ -367,13 +412,14 @@ __global__ __launch_bounds__(256) void k_wsum(WsumArgs a) {
     uint32_t rowbase = 0;
     for (int k = 0; k < a.rr; ++k)
       if (k != a.k_lane && k != a.k_loop) rowbase += (uint32_t)r[k] * (uint32_t)a.ostr_rep[k];
-    // A row of the tile is BJ points: with BJ = 32 the two halves of a wave
-    // take rows r and r + 32 (33 * 32 = 32 mod 64 banks apart: no conflict).
+    // A row of the tile is BJ points: 64 / BJ rows per wave (with BJ = 32 the
+    // halves take rows r and r + 32, 33 * 32 = 32 mod 64 banks apart: no
+    // conflict).
     constexpr int HALVES = 64 / BJ;
     const int col = lane % BJ, half = lane / BJ;
     const int rl = bp * BJ + col;
     const uint32_t sl = (uint32_t)a.ostr_rep[a.k_lane];
-    const int row0 = wave + half * 32;
+    const int row0 = wave + half * (64 / HALVES);
     uint32_t of = rowbase + (uint32_t)(bl * 64 + row0) * sl + (uint32_t)rl * (uint32_t)a.ostr_rep[a.k_loop];
     const bool col_ok = rl < a.R[a.k_loop];
     for (int row = row0; row < row0 + 64 / HALVES; row += 4, of += 4 * sl) {
@@ -385,17 +431,18 @@ __global__ __launch_bounds__(256) void k_wsum(WsumArgs a) {
 using WsumFn = void (*)(WsumArgs);
 
 static WsumFn wsum_pick(const WsumArgs& a) {
-  if (!a.use_box) return k_wsum<false, 0>;
+  if (!a.use_box) return k_wsum<false, 0, 1>;
   switch (a.cls ? a.em : 0) {
-    case 3: return k_wsum<true, 3>;
-    case 5: return k_wsum<true, 5>;
-    case 8: return k_wsum<true, 8>;
-    default: return k_wsum<true, 0>;
+    case 3: return k_wsum<true, 3, kWsumBoxPoints>;
+    case 5: return k_wsum<true, 5, kWsumBoxPoints>;
+    case 8: return k_wsum<true, 8, kWsumBoxPoints>;
+    default: return k_wsum<true, 0, kWsumBoxPoints>;
   }
 }
 
 hipError_t wsum_prepare() {
-  for (WsumFn f : {k_wsum<true, 0>, k_wsum<true, 3>, k_wsum<true, 5>, k_wsum<true, 8>}) {
+  for (WsumFn f : {k_wsum<true, 0, kWsumBoxPoints>, k_wsum<true, 3, kWsumBoxPoints>, k_wsum<true, 5, kWsumBoxPoints>,
+                   k_wsum<true, 8, kWsumBoxPoints>}) {
     hipError_t e = hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        2 * kWsumBoxMaxBytes + 256);
     if (e != hipSuccess) return e;
