@@ -234,7 +234,10 @@ static aol_status wsum_create(const aol_tiler* in, const aol_tiler* out, const f
     return fail(AOL_ERR_UNSUPPORTED, "repetition space needs too many workgroups");
   }
 
-  // Staged form: the box of input elements one block of points (64 x 4 * kWsumBoxPoints) reads,
+  // Staged form: the box of input elements one block of points reads, with
+  // eight points per thread, else with four (29 x 885 x 911, 15 elements: 179
+  // us against 277 by the direct form; two points a thread read too many
+  // elements twice: 11 x 665 x 158, 9 elements, 11.3 against 6.5),
   // when it is small enough for LDS and no pattern spans an array extent.
   {
     bool fit = true;
@@ -248,20 +251,28 @@ static aol_status wsum_create(const aol_tiler* in, const aol_tiler* out, const f
         a.Ps[d][k] = (int64_t)v * 2 > a.S[d] ? v - a.S[d] : v;
       }
     }
+    const bool whole = fit && p->in_elems * 4 < (1LL << 32);
     int64_t elems = 1;
-    for (int d = 0; d < a.ra && fit; ++d) {
-      int64_t ext = fmax[d] - fmin[d] + 1, lo = fmin[d];
-      for (int k : {k_lane, k_loop}) {
-        const int64_t span = (int64_t)a.Ps[d][k] * (k == k_lane ? 63 : 4 * kWsumBoxPoints - 1);
-        ext += span < 0 ? -span : span;
-        lo += span < 0 ? span : 0;
+    fit = false;
+    for (int pts : {kWsumBoxPoints, kWsumBoxPoints / 2}) {
+      if (fit || !whole) break;
+      fit = true;
+      elems = 1;
+      a.points = pts;
+      for (int d = 0; d < a.ra && fit; ++d) {
+        int64_t ext = fmax[d] - fmin[d] + 1, lo = fmin[d];
+        for (int k : {k_lane, k_loop}) {
+          const int64_t span = (int64_t)a.Ps[d][k] * (k == k_lane ? 63 : 4 * pts - 1);
+          ext += span < 0 ? -span : span;
+          lo += span < 0 ? span : 0;
+        }
+        fit = fit && ext <= 2 * (int64_t)a.S[d];  // a box longer than the array holds some elements twice
+        a.bn[d] = (int32_t)std::min<int64_t>(ext, INT32_MAX);
+        a.dlo[d] = (int32_t)lo;
+        elems *= std::min<int64_t>(ext, 1 << 20);
+        fit = fit && elems * 4 <= kWsumBoxMaxBytes;
       }
-      fit = fit && ext <= 2 * (int64_t)a.S[d];  // a box longer than the array holds some elements twice
-      a.bn[d] = (int32_t)ext;
-      a.dlo[d] = (int32_t)lo;
-      elems *= ext;
     }
-    fit = fit && elems * 4 <= kWsumBoxMaxBytes && p->in_elems * 4 < (1LL << 32);
     if (fit) {
       // Rows in whole chunks unless they are so short that the padding would
       // outgrow LDS (a chunk also has to wrap at most once).
@@ -301,8 +312,8 @@ static aol_status wsum_create(const aol_tiler* in, const aol_tiler* out, const f
       }
     }
     a.use_box = fit ? 1 : 0;
-    if (fit) {  // blocks of 64 x 4*kWsumBoxPoints points
-      const int64_t nb = (R[k_loop] + 4 * kWsumBoxPoints - 1) / (4 * kWsumBoxPoints);
+    if (fit) {  // blocks of 64 x 4 * points points
+      const int64_t nb = (R[k_loop] + 4 * a.points - 1) / (4 * a.points);
       blocks = blocks / a.nb_loop * nb;
       a.nb_loop = (int32_t)nb;
       if (blocks >= (1LL << 31)) {
@@ -328,7 +339,7 @@ static aol_status wsum_create(const aol_tiler* in, const aol_tiler* out, const f
         std::vector<int32_t> tab;
         tab.reserve((size_t)total);
         for (int k = 0; k < a.rr; ++k) {
-          const int64_t ext = k == k_lane ? 64 : k == k_loop ? 4 * kWsumBoxPoints : 1;
+          const int64_t ext = k == k_lane ? 64 : k == k_loop ? 4 * a.points : 1;
           a.ctab_off[k] = (int32_t)tab.size();
           for (int64_t b = 0; b < nb[k]; ++b)
             for (int d = 0; d < a.ra; ++d) tab.push_back((int32_t)pmod64((int64_t)a.Ps[d][k] * (b * ext), a.S[d]));
@@ -365,7 +376,8 @@ static aol_status wsum_create(const aol_tiler* in, const aol_tiler* out, const f
         for (int w : kWsumClassWidths)
           if (!em && width <= w) em = w;
         // worth it when a class shares reads (fewer reads than one per element and point)
-        if (js != 0 && em && (int64_t)keys.size() * (em + kWsumBoxPoints - 1) < (int64_t)npat * kWsumBoxPoints) {
+        if (js != 0 && em && a.points == kWsumBoxPoints &&
+            (int64_t)keys.size() * (em + kWsumBoxPoints - 1) < (int64_t)npat * kWsumBoxPoints) {
           a.ctab_cls = (int32_t)tab.size();
           for (size_t c = 0; c < keys.size(); ++c) {
             int64_t lo_m = members[c][0].first;

@@ -27,6 +27,7 @@ struct WsumArgs {
   int32_t Po_loop[kWsumMaxRank];
   int64_t ostr_rep[kWsumMaxRank];        // identity output: stride of each repetition dim
   int32_t k_lane, k_loop;                // repetition dims along lanes / along each thread's loop
+  int32_t points;                        // points per thread along k_loop
   int32_t small;                         // the points' unwrapped base indices, from Ps, fit 32 bits
   int32_t nb_lane, nb_loop;              // blocks along k_lane (64 wide) / k_loop
   uint32_t mg_lane, mg_loop, mg_R[kWsumMaxRank];  // floor(2^32 / divisor) + 1 of nb_lane, nb_loop, R
@@ -71,6 +72,6 @@ struct WsumArgs {
 constexpr int kWsumClassWidths[] = {3, 5, 8};  // kernel instances by the widest class
 
 constexpr int kWsumBoxMaxBytes = 48 * 1024;  // box in LDS per workgroup
-constexpr int kWsumBoxPoints = 8;            // staged form: points per thread along the loop dimension
+constexpr int kWsumBoxPoints = 8;            // staged form: points per thread along the loop dimension at most
 
 }  // namespace aol

@@ -432,6 +432,7 @@ using WsumFn = void (*)(WsumArgs);
 
 static WsumFn wsum_pick(const WsumArgs& a) {
   if (!a.use_box) return k_wsum<false, 0, 1>;
+  if (a.points < kWsumBoxPoints) return k_wsum<true, 0, kWsumBoxPoints / 2>;
   switch (a.cls ? a.em : 0) {
     case 3: return k_wsum<true, 3, kWsumBoxPoints>;
     case 5: return k_wsum<true, 5, kWsumBoxPoints>;
@@ -442,7 +443,7 @@ static WsumFn wsum_pick(const WsumArgs& a) {
 
 hipError_t wsum_prepare() {
   for (WsumFn f : {k_wsum<true, 0, kWsumBoxPoints>, k_wsum<true, 3, kWsumBoxPoints>, k_wsum<true, 5, kWsumBoxPoints>,
-                   k_wsum<true, 8, kWsumBoxPoints>}) {
+                   k_wsum<true, 8, kWsumBoxPoints>, k_wsum<true, 0, kWsumBoxPoints / 2>}) {
     hipError_t e = hipFuncSetAttribute((const void*)f, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        2 * kWsumBoxMaxBytes + 256);
     if (e != hipSuccess) return e;

@@ -47,6 +47,14 @@ def test_staged_rows(w, step, k):
         _case((h, w), (h, -(-w // step)), (3, k), origin, [[1, 0], [0, step]], [[1, 0], [0, -1]])
 
 
+@pytest.mark.parametrize("n", [33, 45, 48])
+def test_staged_narrow_blocks(n):
+    """Boxes that fit with 16 points of the second dimension a block, not with 32."""
+    for flip in (False, True):
+        _case((6, 2 * n, 201), (6, n, 101), (3, 1), (5, 2 * n - 3, 7), [[1, 0, 0], [0, 2, 0], [0, 0, 2]],
+              [[1, 0], [0, 0], [0, 0]], flip)
+
+
 @pytest.mark.parametrize("pat", [(1, 1), (7, 1), (2, 4), (3, 3), (3, 5), (4, 4), (8, 8)])
 @pytest.mark.parametrize("rep", [(3, 64, 4), (5, 65, 5), (2, 63, 3), (1, 130, 9)])
 def test_direct_sheared(pat, rep):
