@@ -37,6 +37,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "generic.h"
 
 namespace aol {
@@ -137,8 +139,9 @@ __device__ __forceinline__ void wsum_box_classes(const WsumArgs& a, const float*
 template <bool BOX, int EM, int PT>
 __global__ __launch_bounds__(256) void k_wsum(WsumArgs a) {
   constexpr int BJ = 4 * PT;  // block extent along the loop dimension
-  __shared__ float tile[64][BJ + 1];
+  constexpr int TP = BJ + 1;  // pitch of the transposed tile (in the box's place once its sums are done)
   extern __shared__ __attribute__((aligned(16))) float box[];
+  float* tile = box;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
@@ -341,8 +344,9 @@ __global__ __launch_bounds__(256) void k_wsum(WsumArgs a) {
 
   if constexpr (BOX) {
     if (a.transpose) {  // the usual staged case: results go through the transposed tile
+      __syncthreads();
 #pragma unroll
-      for (int j = 0; j < PT; ++j) tile[lane][wave * PT + j] = bacc[j];
+      for (int j = 0; j < PT; ++j) tile[lane * TP + wave * PT + j] = bacc[j];
     }
   }
 #pragma unroll(BOX ? PT : 1)
@@ -381,7 +385,7 @@ __global__ __launch_bounds__(256) void k_wsum(WsumArgs a) {
       }
     }
     if (a.transpose) {
-      tile[lane][wave * PT + j] = acc;
+      tile[lane * TP + wave * PT + j] = acc;
     } else if (ok) {
       int64_t of = oflat;
       if (!a.out_identity) {
@@ -423,7 +427,7 @@ __global__ __launch_bounds__(256) void k_wsum(WsumArgs a) {
     uint32_t of = rowbase + (uint32_t)(bl * 64 + row0) * sl + (uint32_t)rl * (uint32_t)a.ostr_rep[a.k_loop];
     const bool col_ok = rl < a.R[a.k_loop];
     for (int row = row0; row < row0 + 64 / HALVES; row += 4, of += 4 * sl) {
-      if (col_ok && bl * 64 + row < a.R[a.k_lane]) ((gout_t)a.out)[of] = tile[row][col];
+      if (col_ok && bl * 64 + row < a.R[a.k_lane]) ((gout_t)a.out)[of] = tile[row * TP + col];
     }
   }
 }
@@ -452,8 +456,9 @@ hipError_t wsum_prepare() {
 }
 
 hipError_t wsum_launch(const WsumArgs& a, int64_t blocks, hipStream_t stream) {
-  // the box, one spill slot per lane, then the row offsets
-  const size_t lds = a.use_box ? (size_t)(a.box_elems + 64 + a.box_rows) * 4 : 0;
+  // the box, one spill slot per lane, then the row offsets; or the transposed tile
+  size_t lds = a.use_box ? (size_t)(a.box_elems + 64 + a.box_rows) * 4 : 0;
+  if (a.transpose) lds = std::max(lds, (size_t)64 * (4 * (a.use_box ? a.points : 1) + 1) * 4);
   hipLaunchKernelGGL(wsum_pick(a), dim3((unsigned)blocks), dim3(256), lds, stream, a);
   return hipGetLastError();
 }
