@@ -363,9 +363,9 @@ aol_status aol_batch_buffers_destroy(aol_buffer_set* set);
 aol_status aol_autotune(aol_batch_plan* plan, hipStream_t stream);
 
 /* Rebuilds the plan with one schedule: segments of seg_reps repetitions (a
- * multiple of 16; 0: about 512 input lines, shortened for streams whose units
- * would exceed a workgroup's fair share) and column bands that fit
- * lds_budget bytes of LDS per workgroup (16 KiB .. 160 KiB). A configuration
+ * multiple of 16; 0: about 240 input lines, shorter for few streams) and, for
+ * streams of 4 GiB or more, column bands that fit lds_budget bytes of LDS per
+ * workgroup (16 KiB .. 160 KiB). A configuration
  * call, not a run call: it waits for all work on the device (launches in
  * flight read the tables it rewrites), then uploads; graphs captured before it
  * must be captured again. AOL_ERR_UNSUPPORTED when the schedule does not fit; the
@@ -374,10 +374,9 @@ aol_status aol_autotune(aol_batch_plan* plan, hipStream_t stream);
 aol_status aol_batch_set_schedule(aol_batch_plan* plan, int32_t seg_reps, int32_t lds_budget);
 
 /* Rebuilds the plan with the current schedule and a new weight (per mille,
- * 250 .. 4000; 1000 after aol_batch_set_schedule) of the int8-tap streams'
- * estimated cost when they and the split-tap streams share one launch: a
- * larger weight gives the int8-tap part more of the device's workgroups. No
- * effect on a plan with one part. A configuration call like
+ * 250 .. 4000; 1000 after aol_batch_set_schedule) of the int8-tap streams. The
+ * weight is kept with the schedule and in the tuning cache; the kernels share
+ * the device between all streams without it. A configuration call like
  * aol_batch_set_schedule (graphs must be captured again; AOL_ERR_INVALID for
  * a weight out of range, the previous schedule stays in place). Results are
  * identical for every weight. */

@@ -969,19 +969,7 @@ __global__ __launch_bounds__(kBandThreads) void k_band(BandLaunch L) {
   band_body<ELEM, SLOTS, SPLIT, KM, GATHER>(L, lds);
 }
 
-// One launch of two parts of an integer batch on disjoint workgroups: the
-// first A.ngroups workgroups run the streams whose taps fit int8, the others
-// those whose taps are split (each part with its own kernel body, units and
-// balanced schedule).
-template <int SLOTS_A, int SLOTS_B, int KM>
-__global__ __launch_bounds__(kBandThreads) void k_band_dual(BandLaunch A, BandLaunch B) {
-  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-  if ((int)blockIdx.x < B.wg0) band_body<kU8, SLOTS_A, false, KM, false>(A, lds);
-  else band_body<kU8, SLOTS_B, true, KM, false>(B, lds);
-}
-
 using BandFn = void (*)(BandLaunch);
-using BandDualFn = void (*)(BandLaunch, BandLaunch);
 
 template <int ELEM, bool SPLIT, int KM>
 static BandFn band_pick_s(int slots) {
@@ -1025,41 +1013,6 @@ hipError_t band_launch(int elem, int slots, bool split, int kmax, bool gather, c
   La.wg0 = 0;
   La.ngroups = grid;
   hipLaunchKernelGGL(band_pick(elem, slots, split, kmax, gather), dim3(grid), dim3(kBandThreads), lds_bytes, stream, La);
-  return hipGetLastError();
-}
-
-// Instances: staging slots 4 or 8 per part (fewer are served by 4), one or
-// two K-steps.
-template <int KM>
-static BandDualFn band_dual_pick_k(int slots_a, int slots_b) {
-  if (slots_a <= 4) return slots_b <= 4 ? k_band_dual<4, 4, KM> : k_band_dual<4, 8, KM>;
-  return slots_b <= 4 ? k_band_dual<8, 4, KM> : k_band_dual<8, 8, KM>;
-}
-
-static BandDualFn band_dual_pick(int slots_a, int slots_b, int kmax) {
-  return kmax <= 1 ? band_dual_pick_k<1>(slots_a, slots_b) : band_dual_pick_k<2>(slots_a, slots_b);
-}
-
-bool band_dual_supported(int slots_a, int slots_b, int kmax) {
-  return slots_a <= 8 && slots_b <= 8 && kmax <= 2;
-}
-
-hipError_t band_dual_prepare(int slots_a, int slots_b, int kmax, size_t lds_bytes, int* wg_per_cu) {
-  const void* f = (const void*)band_dual_pick(slots_a, slots_b, kmax);
-  hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-  if (e != hipSuccess) return e;
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(wg_per_cu, f, kBandThreads, lds_bytes);
-}
-
-hipError_t band_dual_launch(int slots_a, int slots_b, int kmax, const BandLaunch& A, int grid_a, const BandLaunch& B,
-                            int grid_b, size_t lds_bytes, hipStream_t stream) {
-  BandLaunch La = A, Lb = B;
-  La.wg0 = 0;
-  La.ngroups = grid_a;
-  Lb.wg0 = grid_a;
-  Lb.ngroups = grid_b;
-  hipLaunchKernelGGL(band_dual_pick(slots_a, slots_b, kmax), dim3(grid_a + grid_b), dim3(kBandThreads), lds_bytes,
-                     stream, La, Lb);
   return hipGetLastError();
 }
 

@@ -28,9 +28,8 @@ struct Schedule {
   int seg = 0;         // repetitions per segment (0: about 512 input lines)
   int budget = 150 * 1024;  // LDS budget per workgroup (picks the column band)
   std::vector<int> class_seg;  // per stream class: its own segment length (0 or absent: seg)
-  // Per mille: weight of the int8-tap part's estimated cost when one launch
-  // divides the device's workgroups between the two parts (the estimate
-  // misjudges the two bodies' relative speed by some tens of percent).
+  // Per mille: weight of the int8-tap streams, kept with the schedule and its
+  // saved form; every kernel of a batch shares the device without it.
   int part_weight = 1000;
 };
 constexpr int kPartWeightMin = 250, kPartWeightMax = 4000;
@@ -93,10 +92,6 @@ struct aol_batch_plan {
     DeviceBuf d_units;
   };
   StripPart sparts[2];                // whole chunks, edges
-  // Both parts in one launch (k_band_dual): each on its own share of the
-  // workgroups, in proportion to its estimated cost.
-  bool dual = false;
-  size_t dual_lds = 0;
   Schedule sched;
   std::vector<BandStream> streams;
   DeviceBuf d_streams, d_table;
@@ -356,10 +351,6 @@ static aol_status batch_build(aol_batch_plan* bp, const Schedule& sc) {
     aol_status st = batch_build_part(bp, P, sc, streams);
     if (st) return st;
   }
-  aol_batch_plan::Part &A = bp->parts[0], &B = bp->parts[1];
-  const int kmax = std::max(A.kmax, B.kmax);
-  bp->dual = !bp->strips && bp->elem == kU8 && !A.ids.empty() && !B.ids.empty() && !A.gather && !B.gather &&
-             band_dual_supported(A.slots, B.slots, kmax);
   if (bp->strips) {
     if (aol_status st = batch_place_strips(bp, sc)) return st;
     for (const aol_batch_plan::StripPart& P : bp->sparts) {
@@ -369,31 +360,6 @@ static aol_status batch_build(aol_batch_plan* bp, const Schedule& sc) {
       lds = std::max(lds, (int)P.lds);
       ++launches;
     }
-  } else if (bp->dual) {
-    // one launch: the device's resident workgroups split between the parts
-    // in proportion to their estimated costs
-    bp->dual_lds = std::max(A.lds, B.lds);
-    int wg = 0, dev = 0, cus = 0;
-    hipError_t e = band_dual_prepare(A.slots, B.slots, kmax, bp->dual_lds, &wg);
-    if (e != hipSuccess) return hip_fail(e, "band kernel attributes");
-    if ((e = hipGetDevice(&dev)) != hipSuccess) return hip_fail(e, "hipGetDevice");
-    if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
-      return hip_fail(e, "hipDeviceGetAttribute");
-    const int total = wg * cus;
-    if (total < 2) return fail(AOL_ERR_UNSUPPORTED, "batch schedule does not fit a compute unit");
-    double ca = 0, cb = 0;
-    for (int64_t c : A.cost) ca += (double)c;
-    for (int64_t c : B.cost) cb += (double)c;
-    ca *= sc.part_weight / 1000.0;
-    int ga = (int)(total * ca / std::max(ca + cb, 1.0) + 0.5);
-    ga = std::max(1, std::min(total - 1, ga));
-    aol_status st = batch_place_part(A, ga);
-    if (!st) st = batch_place_part(B, total - ga);
-    if (st) return st;
-    units = (int)(A.units.size() + B.units.size());
-    grid = A.grid + B.grid;
-    lds = (int)bp->dual_lds;
-    launches = 1;
   } else {
     for (aol_batch_plan::Part& P : bp->parts) {
       if (P.ids.empty()) continue;
@@ -451,13 +417,6 @@ static aol_status batch_launch(aol_batch_plan* bp, hipStream_t stream, const voi
       hipError_t h = strip_batch_launch(bp->elem, e == 1, L, P.units, P.lds, stream);
       if (h != hipSuccess) return hip_fail(h, "batch kernel launch");
     }
-    return AOL_OK;
-  }
-  if (bp->dual) {
-    const aol_batch_plan::Part &A = bp->parts[0], &B = bp->parts[1];
-    hipError_t e = band_dual_launch(A.slots, B.slots, std::max(A.kmax, B.kmax), part_launch(bp, A, table), A.grid,
-                                    part_launch(bp, B, table), B.grid, bp->dual_lds, stream);
-    if (e != hipSuccess) return hip_fail(e, "batch kernel launch");
     return AOL_OK;
   }
   for (const aol_batch_plan::Part& P : bp->parts) {
@@ -863,18 +822,6 @@ aol_status aol_autotune(aol_batch_plan* plan, hipStream_t stream) {
     }
     return st == AOL_OK;
   };
-  // the weight of the int8-tap part when both parts share one launch
-  auto weights = [&](std::initializer_list<int> deltas) {
-    if (best_ms >= 1e30f || batch_build(plan, best) != AOL_OK || !plan->dual) return true;
-    const Schedule base = best;
-    for (int d : deltas) {
-      Schedule sc = base;
-      sc.part_weight = base.part_weight + d;
-      if (sc.part_weight < kPartWeightMin || sc.part_weight > kPartWeightMax) continue;
-      if (!trial(sc)) return false;
-    }
-    return true;
-  };
   // 1. one segment length and LDS budget (column band) for every stream
   const int segs[] = {16, 32, 64, 128};
   const int budgets[] = {150 * 1024, 76 * 1024};
@@ -887,9 +834,7 @@ aol_status aol_autotune(aol_batch_plan* plan, hipStream_t stream) {
       sc.budget = budget;
       if (go) go = trial(sc);
     }
-  // 2. the parts' weight, coarse
-  if (go) go = weights({-500, -400, -300, -200, -100, 100, 250, 500});
-  // 3. each stream class's own segment length, classes with the most input
+  // 2. each stream class's own segment length, classes with the most input
   // first, the others held at their best so far (one pass)
   if (go && best_ms < 1e30f) {
     std::vector<int> order(plan->cls_bytes.size());
@@ -907,8 +852,6 @@ aol_status aol_autotune(aol_batch_plan* plan, hipStream_t stream) {
       }
     }
   }
-  // 4. the parts' weight again, fine, around the best
-  if (go) go = weights({-100, -50, 50, 100});
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (st) return st;

@@ -720,10 +720,10 @@ static aol_status run_strips(aol_plan* plan, int32_t n_frames, const void* const
   // against 0.229 ms); the wide form's share fewer, and it runs better with all
   // XCDs in the same frames (300 frames at 3/8: 0.232 against 0.239).
   L.by_xcd = form == kStripUsual && total <= kStripMaxGrid ? 1 : 0;
-  for (int first = 0; first < total; first += kStripMaxGrid) {
-    L.first = first;
+  for (int64_t first = 0; first < total; first += kStripMaxGrid) {
+    L.first = (int32_t)first;
     hipError_t e = strip_launch(plan->elem, plan->strips.cls, form, plan->sedges, L,
-                                std::min(total - first, kStripMaxGrid), plan->strips.lds[form], stream);
+                                (int)std::min<int64_t>(total - first, kStripMaxGrid), plan->strips.lds[form], stream);
     if (e != hipSuccess) return hip_fail(e, "strip kernel launch");
   }
   return ok();
