@@ -716,10 +716,14 @@ static aol_status run_strips(aol_plan* plan, int32_t n_frames, const void* const
   L.wgs_per_frame = (int32_t)wgs;
   L.mg_wgs = strip_magic(L.wgs_per_frame);
   // Workgroups that share lines (neighbours in a row, the segments of a
-  // column) on one XCD, for its L2 (200 frames of 1920x1080 at 2/3: 0.218
-  // against 0.229 ms); the wide form's share fewer, and it runs better with all
-  // XCDs in the same frames (300 frames at 3/8: 0.232 against 0.239).
-  L.by_xcd = form == kStripUsual && total <= kStripMaxGrid ? 1 : 0;
+  // column) on one XCD, for its L2: all of a short launch in consecutive
+  // items (19 frames of 2160x1217 at 2/3: 77 us, in runs of 16 79, in order
+  // 87). A launch of many rounds runs better with all XCDs in the same frames:
+  // runs of 16 items, or 8 of the wide form (277 frames of 1280x720 at 1/2: 119
+  // us, consecutive 120, in order 121; 300 of 1920x1080 at 3/8, wide: 230, 234
+  // in order, 239 consecutive; 143 of 1584x993 fp16 at 1/2, wide: 222, 236 in
+  // order).
+  L.by_xcd = form == kStripWide ? 3 : total >= 4 * plan->cus * plan->strips.resident ? 4 : -1;
   for (int64_t first = 0; first < total; first += kStripMaxGrid) {
     L.first = (int32_t)first;
     hipError_t e = strip_launch(plan->elem, plan->strips.cls, form, plan->sedges, L,

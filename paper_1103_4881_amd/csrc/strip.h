@@ -92,7 +92,7 @@ struct StripLaunch {
   int32_t n_planes, wgs_per_frame;
   uint32_t mg_wgs;               // floor(2^32 / wgs_per_frame) + 1
   int32_t first;                 // the launch's first workgroup (a large launch is cut)
-  int32_t by_xcd;                // the workgroups of one XCD take consecutive items (first is 0)
+  int32_t by_xcd;                // items of one XCD: consecutive ones (-1, first is 0) or in runs of 2^by_xcd
 };
 
 }  // namespace aol

@@ -14,6 +14,14 @@ __device__ __forceinline__ int strip_item(int x, int total) {
   return xcd * per + min(xcd, rem) + (x >> 3);
 }
 
+// The same in runs of 2^s consecutive items per XCD: neighbours in a row share
+// their lines, and all XCDs stay in the same frames.
+__device__ __forceinline__ int strip_run(int x, int total, int s) {
+  const int block = 8 << s;
+  if ((x | (block - 1)) >= total) return x;  // the launch's last items in order
+  return (x & ~(block - 1)) + ((x & 7) << s) + ((x & (block - 1)) >> 3);
+}
+
 }  // namespace
 
 // Waves per SIMD the registers are held to: four (128 registers) where the
@@ -28,7 +36,7 @@ __global__ __launch_bounds__(64 * W, strip_occ(ELEM, SPLIT, KH, KV, EDGES)) void
   constexpr int ES = ELEM == kU8 ? 1 : 2, OES = ELEM == kU8 ? 1 : 4;
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   const STRIP_CONST StripLaunch* A = (const STRIP_CONST StripLaunch*)__builtin_amdgcn_kernarg_segment_ptr();
-  const int item = L.by_xcd ? strip_item(blockIdx.x, gridDim.x) : (int)blockIdx.x + L.first;
+  const int item = L.by_xcd < 0 ? strip_item(blockIdx.x, gridDim.x) : strip_run(blockIdx.x, gridDim.x, L.by_xcd) + L.first;
   const int frame = div_by(item, L.wgs_per_frame, L.mg_wgs);
   int r = item - frame * L.wgs_per_frame;
   int pl = 0;
