@@ -70,8 +70,9 @@ def check_frames(n):
 
 # ------------------------------------------------------------------ HBM traffic from counters
 
-KERNEL_SOURCES = ["paper_1103_4881_amd/csrc/band.hip", "paper_1103_4881_amd/csrc/aol_internal.h"]
-TRAFFIC_FILE = "profiles/k_band_u8_i420_1080p_300f_traffic.json"
+KERNEL_SOURCES = ["paper_1103_4881_amd/csrc/strip.hip", "paper_1103_4881_amd/csrc/strip_body.h",
+                  "paper_1103_4881_amd/csrc/strip.h", "paper_1103_4881_amd/csrc/aol_internal.h"]
+TRAFFIC_FILE = "profiles/k_strip_u8_i420_1080p_300f_traffic.json"
 
 
 def kernel_hash():
@@ -783,7 +784,7 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(gbs / HBM_PEAK_GBS, 4), "traffic": traffic_bytes() if u8 else None,
                      "copy_peak": copy, "frac_of_copy": round(gbs / copy, 4) if copy else None,
-                     "kernel": "aol::k_band<u8>" if u8 else f"aol::k_band<{dtype}>",
+                     "kernel": "aol::k_strip<u8>" if u8 else f"aol::k_strip<{dtype}>",
                      "alg_bytes_per_launch": main_res["bytes"],
                      "kernel_ms_mean": round(main_res["ms_kernel"], 4),
                      "kernel_ms_median": round(main_res["ms_kernel_median"], 4)},

@@ -143,16 +143,16 @@ aol_status aol_plan_destroy(aol_plan* plan);
  * Rebuilds the plan's tables like aol_plan_set_band (capture graphs again). */
 aol_status aol_plan_set_tile(aol_plan* plan, int32_t tile_rx, int32_t tile_ry);
 
-/* Band schedule (the default for every plan that fits it): a workgroup owns a
- * column band of band_reps repetitions (0: the widest that fits a compute
- * unit, normally the full width) and streams segments of seg_reps
- * repetitions down the plane, keeping the intermediate in an LDS ring.
- * seg_reps 0: the plan keeps unit lists for segments of about 512, 256, 128
- * and 64 input lines, and each launch takes the longest that leaves every
- * resident workgroup about four units. Multiples of 16. This call (like plan
- * creation) builds and uploads those lists synchronously; it frees the
- * previous ones, so a graph captured from an earlier run of this plan must
- * be captured again. Selecting a band re-selects the band kernel after
+/* Schedule of the streaming kernels (the default for every plan): workgroups
+ * walk segments of seg_reps repetitions down the plane. seg_reps 0: each
+ * launch chooses its segments from the frame count. Planes of 4 GiB or more
+ * run on column bands of band_reps repetitions (0: the widest that fits a
+ * compute unit, normally the full width), the intermediate in an LDS ring;
+ * other planes on strips of output columns, the intermediate in registers,
+ * for which band_reps is checked only. Multiples of 16. This call (like plan
+ * creation) builds and uploads the bands' unit lists synchronously; it frees
+ * the previous ones, so a graph captured from an earlier run of this plan must
+ * be captured again. It re-selects the streaming kernels after
  * aol_plan_set_tile. AOL_ERR_UNSUPPORTED if the band does not fit. Results
  * are identical for every schedule. */
 aol_status aol_plan_set_band(aol_plan* plan, int32_t band_reps, int32_t seg_reps);
@@ -275,7 +275,8 @@ aol_status aol_pipeline_run_u8(aol_pipeline* pipe, int32_t n_frames, const uint8
  * Batches of video streams (Sec. III: the downscaler repeats for every frame;
  * Sec. III-A: all elementary tasks are independent, so frames of different
  * streams may run together). One step downscales one frame of every stream,
- * each with its own size and filter pair, in one persistent launch.
+ * each with its own size and filter pair, in one launch (two if the lines of
+ * some streams only are whole 16-byte chunks).
  *
  * Device pointers live in a plan-owned device table written by
  * aol_batch_set_pointers (a small enqueued kernel: no host synchronisation),
@@ -350,13 +351,11 @@ aol_status aol_batch_run_buffers(aol_batch_plan* plan, const aol_buffer_set* set
 aol_status aol_batch_buffers_destroy(aol_buffer_set* set);
 
 /* Times schedule candidates on the buffers last set: first one segment
- * length for every stream x the column-band LDS budget (16..128 repetitions x
- * 150 or 76 KiB); then, where the int8-tap and split-tap streams share one
- * launch, the weight of the int8-tap part in the division of the workgroups
- * (500..1500 per mille); then, classes with the most input first, each stream
- * class's own segment length (16..128; a class: the two ratios and the width
- * class up to 640, 1280, 1920 pixels or wider) with the others held; last the
- * weight again within 100 per mille of the best. Keeps the fastest and appends
+ * length for every stream (16..128 repetitions; with streams of 4 GiB or more
+ * also the column-band LDS budget, 150 or 76 KiB); then, classes with the most
+ * input first, each stream class's own segment length (16..128; a class: the
+ * two ratios and the width class up to 640, 1280, 1920 pixels or wider) with
+ * the others held. Keeps the fastest and appends
  * it to the tuning cache (keyed by the device architecture, the precision and
  * the streams' sizes and filters). Synchronises the stream (not a run call);
  * results are unchanged. */
