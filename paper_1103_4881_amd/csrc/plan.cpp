@@ -468,6 +468,9 @@ static aol_status plan_build_band(aol_plan* pl, int xreps, int seg) {
       if (!build_strip_stream(pl->strips, d.height, d.width, d.in_pitch, d.out_pitch, pl->sstreams[i])) pl->strips.cls = -1;
       pl->sedges = pl->sedges || strip_edges(pl->strips, pl->sstreams[i]);
     }
+    // the edge instances hold three workgroups at most (32 frames of 1366x768 at
+    // 1/2, planned for four 43 us, for three 39)
+    if (pl->sedges) pl->strips.resident = std::min(pl->strips.resident, 3);
     for (int f = 0; f < kStripForms && pl->strips.cls >= 0; ++f) {
       if (f == kStripWide && pl->sedges) pl->strips.wnb[f] = 0;  // (no such instance)
       if (!pl->strips.wnb[f]) continue;
