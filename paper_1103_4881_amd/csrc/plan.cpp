@@ -465,8 +465,10 @@ static aol_status plan_build_band(aol_plan* pl, int xreps, int seg) {
     pl->sedges = false;
     for (int i = 0; i < pl->n_planes && pl->strips.cls >= 0; ++i) {
       const aol_plane_desc& d = pl->planes[i];
-      if (!build_strip_stream(pl->strips, d.height, d.width, d.in_pitch, d.out_pitch, pl->sstreams[i])) pl->strips.cls = -1;
-      pl->sedges = pl->sedges || strip_edges(pl->strips, pl->sstreams[i]);
+      if (build_strip_stream(pl->strips, d.height, d.width, d.in_pitch, d.out_pitch, pl->sstreams[i]))
+        pl->sedges = pl->sedges || strip_edges(pl->strips, pl->sstreams[i]);
+      else
+        pl->strips.cls = -1;
     }
     // the edge instances hold three workgroups at most (32 frames of 1366x768 at
     // 1/2, planned for four 43 us, for three 39)
@@ -850,17 +852,23 @@ aol_status aol_downscale_u8(aol_plan* plan, int32_t n_frames, const uint8_t* con
 
 const char* aol_plan_schedule(aol_plan* plan, int32_t n_frames) {
   if (!plan) return "";
-  char buf[320];
+  char buf[400];
   if (plan->use_band) {
     const aol_plan::BandSched* sc = band_pick_sched(plan, std::max(1, (int)n_frames));
     const int64_t items = (int64_t)sc->units * std::max(1, (int)n_frames);
-    int segb = 0;
-    const int form = strip_form(plan, std::max(1, (int)n_frames), sc, &segb);
-    snprintf(buf, sizeof buf,
-             "{\"kernel\": \"band\", \"seg\": %d, \"units_per_frame\": %d, \"items\": %lld, \"grid\": %lld, "
-             "\"slots\": %d, \"kmax\": %d, \"split\": %d, \"lds\": %zu, \"form\": %d, \"seg_blocks\": %d}",
-             sc->seg, sc->units, (long long)items, (long long)std::min<int64_t>(items, plan->bgrid), plan->bslots,
-             plan->fbands.kmax, plan->fbands.split ? 1 : 0, plan->blds, form, segb);
+    const int at =
+        snprintf(buf, sizeof buf,
+                 "{\"kernel\": \"band\", \"seg\": %d, \"units_per_frame\": %d, \"items\": %lld, \"grid\": %lld, "
+                 "\"slots\": %d, \"kmax\": %d, \"split\": %d, \"lds\": %zu",
+                 sc->seg, sc->units, (long long)items, (long long)std::min<int64_t>(items, plan->bgrid), plan->bslots,
+                 plan->fbands.kmax, plan->fbands.split ? 1 : 0, plan->blds);
+    if (plan->strips.cls >= 0) {
+      int segb = 0;
+      const int form = strip_form(plan, std::max(1, (int)n_frames), sc, &segb);
+      snprintf(buf + at, sizeof buf - at, ", \"form\": %d, \"seg_blocks\": %d}", form, segb);
+    } else {
+      snprintf(buf + at, sizeof buf - at, "}");
+    }
   } else {
     snprintf(buf, sizeof buf, "{\"kernel\": \"tiled\", \"tile\": [%d, %d], \"lds\": %zu}", plan->trx, plan->try_,
              plan->lds);

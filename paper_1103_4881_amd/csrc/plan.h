@@ -68,7 +68,7 @@ struct aol_plan {
   std::vector<BandSched> bsched;
   // strip kernel (runs the band schedule; strips.cls < 0: not available)
   StripTables strips;
-  StripStream sstreams[kMaxPlanes];
+  StripStream sstreams[kMaxPlanes] = {};
   bool sedges = false;  // some plane's lines are not whole 16-byte chunks
   int cus = 0;  // compute units of the device
   std::atomic<uint64_t> pick{0};  // n_frames << 32 | form << 16 | blocks per segment of the last launch

@@ -1,0 +1,25 @@
+"""Host code of plans, schedules and launch shapes on the CPU, with a stand-in for the HIP runtime (no
+kernel runs): calls that must not end the process, and launches that must stay within a grid's limits."""
+
+import pytest
+
+from tests import hip_stub
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("hip_stub")
+    return lambda script: hip_stub.run(tmp, script)
+
+
+@pytest.mark.parametrize("kw", ["[(65536, 65536)]", "[(480, 640)], in_pitches=[1 << 24]",
+                                "[(480, 640)], out_pitches=[1 << 29]", "[(480, 640), (65536, 65536), (480, 640)]"])
+def test_schedule_of_planes_beyond_the_strip_kernel(host, kw):
+    """The schedule of a plan with a plane of 4 GiB or more (or 16 output rows of as much)."""
+    sched = host(f"""
+f = aol.Polyphase(3, 8, synthgen.design_taps(3, 8, 11))
+plan = aol.DownscalePlan({kw}, hf=f, vf=f)
+print(json.dumps([plan.schedule(1), plan.schedule(300)]))
+""")
+    for s, n in zip(sched, (1, 300)):
+        assert s["kernel"] == "band" and s["items"] == n * s["units_per_frame"] > 0, s
