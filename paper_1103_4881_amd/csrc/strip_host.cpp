@@ -187,6 +187,7 @@ uint32_t strip_magic(int d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 3
 bool strip_edges(const StripTables& t, const StripStream& S) { return S.w % (t.elem == kU8 ? 16 : 8) != 0; }
 
 void strip_set_segments(StripStream& S, int wnb, int segb) {
+  segb = std::min(segb, S.nbv);  // (a caller's segment may be any length)
   S.wgx = (S.nbh + wnb - 1) / wnb;
   S.wnb = (S.nbh + S.wgx - 1) / S.wgx;
   S.mg_wgx = strip_magic(S.wgx);

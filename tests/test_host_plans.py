@@ -23,3 +23,16 @@ print(json.dumps([plan.schedule(1), plan.schedule(300)]))
 """)
     for s, n in zip(sched, (1, 300)):
         assert s["kernel"] == "band" and s["items"] == n * s["units_per_frame"] > 0, s
+
+
+def test_batch_segments_of_any_length(host):
+    """The longest segment a caller may name, on streams of many 16-row blocks."""
+    sched = host("""
+f = aol.Polyphase(16, 24, synthgen.design_taps(16, 24, 9))
+plan = aol.BatchPlan([(1080, 1920, f, f), (1080, 1921, f, f)])
+plan.set_schedule(2 ** 31 - 16, 150 * 1024)
+long = json.loads(plan.schedule())
+plan.set_schedule(1024, 150 * 1024)
+print(json.dumps([long, json.loads(plan.schedule())]))
+""")
+    assert sched[0]["seg"] == 2 ** 31 - 16 and sched[0]["units"] == sched[1]["units"] > 0
