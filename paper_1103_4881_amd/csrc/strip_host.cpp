@@ -172,8 +172,10 @@ bool build_strip_stream(const StripTables& t, int64_t h, int64_t w, int64_t in_p
   S.w = (int32_t)w;
   // p outputs per q inputs: per period of 16 repetitions, nblk blocks of 16
   const int64_t qh = (int64_t)F.per_chunks * E / 16, qv = F.per_steps;
-  S.mh = (int32_t)(F.nblk_v * ((h + qv - 1) / qv));
-  S.mw = (int32_t)(F.nblk_h * ((w + qh - 1) / qh));
+  const int64_t mh = F.nblk_v * ((h + qv - 1) / qv), mw = F.nblk_h * ((w + qh - 1) / qh);
+  if (mh > (1 << 30) || mw > (1 << 30)) return false;  // (a plan's sides are checked, a batch's are not)
+  S.mh = (int32_t)mh;
+  S.mw = (int32_t)mw;
   S.col0 = t.col0;
   S.line0 = t.line0;
   S.nbh = (S.mw + 15) / 16;

@@ -26,7 +26,8 @@ struct StripTables {
 aol_status build_strip_tables(const FilterHost& hf, const FilterHost& vf, int elem, StripTables& out);
 
 // Descriptor of one plane or stream (segments: see strip_set_segments).
-// False for planes of 4 GiB or more (the kernel's lane offsets are 32-bit).
+// False for planes of 4 GiB or more (the kernel's lane offsets are 32-bit) and
+// for output sides above 2^30.
 bool build_strip_stream(const StripTables& t, int64_t h, int64_t w, int64_t in_pitch, int64_t out_pitch,
                         StripStream& S);
 

@@ -36,3 +36,15 @@ plan.set_schedule(1024, 150 * 1024)
 print(json.dumps([long, json.loads(plan.schedule())]))
 """)
     assert sched[0]["seg"] == 2 ** 31 - 16 and sched[0]["units"] == sched[1]["units"] > 0
+
+
+def test_batch_output_of_2_32_rows(host):
+    """A stream whose output height is 2^32 (zero in 32 bits) makes a plan or is refused."""
+    units = host("""
+v, h = aol.Polyphase(16, 1, [[256]] * 16), aol.Polyphase(1, 1, [[256]])
+try:
+    print(json.dumps(json.loads(aol.BatchPlan([(1 << 28, 1, h, v)]).schedule())["units"]))
+except aol.AolError as e:
+    print(json.dumps(e.status))
+""")
+    assert units > 0 or units == -2
