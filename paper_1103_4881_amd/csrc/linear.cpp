@@ -245,7 +245,7 @@ void plan_pack(const LinearArgs& a, const aol_tiler* in, const aol_tiler* out, c
       const int64_t S = t->array_shape[d], o = pmod64(t->origin[d], S);
       int64_t lo = o, hi = o, flo = 0, fhi = 0;
       for (int k = 0; k < a.rr; ++k) {
-        if (std::abs(t->paving[d][k]) > S) return;  // (the spans below stay far inside int64)
+        if (t->paving[d][k] > S || t->paving[d][k] < -S) return;  // (the spans below stay far inside int64)
         const int64_t span = t->paving[d][k] * (t->rep_shape[k] - 1);
         (span < 0 ? lo : hi) += span;
         fs[side][k] += t->paving[d][k] * st;
@@ -255,7 +255,7 @@ void plan_pack(const LinearArgs& a, const aol_tiler* in, const aol_tiler* out, c
         fitting_offsets(t, i, f);
         flo = std::min(flo, f[d]);
         fhi = std::max(fhi, f[d]);
-        if (std::abs(f[d]) > S) return;
+        if (f[d] > S || f[d] < -S) return;
         off[side][i] += f[d] * st;
       }
       if (lo + flo < 0 || hi + fhi >= S) return;

@@ -48,3 +48,26 @@ except aol.AolError as e:
     print(json.dumps(e.status))
 """)
     assert units > 0 or units == -2
+
+
+LINEAR = """
+def kernel(shape, rep, pat, origin, paving, fitting, oshape, opaving, ofitting, opat, value=1):
+    n_in, n_out = int(np.prod(pat)), int(np.prod(opat))
+    tin = aol.make_tiler(shape, rep, pat, origin, paving, fitting)
+    tout = aol.make_tiler(oshape, rep, opat, (0,) * len(oshape), opaving, ofitting)
+    plan = aol.aol_linear_plan_create(tin, tout, np.full((n_out, n_in), value))
+    stub.stub_reset()
+    aol.aol_linear_run(plan, BUF, 2 * BUF, 0)
+    aol.aol_linear_plan_destroy(plan)
+    return launches()[0][0]
+"""
+
+
+def test_linear_packed_form_strides(host):
+    """Pavings of -2^63 (a residue of any modulus, but no stride that fits 64 bits) stay off the packed form."""
+    names = host(LINEAR + """
+def rgb(p):
+    return kernel((30000,), (3, 500), (3,), (0,), [[p, 3]], [[1]], (3, 3, 500), [[0, 0], [1, 0], [0, 1]], [[1], [0], [0]], (3,))
+print(json.dumps([rgb(1500), rgb(-2 ** 63)]))
+""")
+    assert "k_linear_pack" in names[0] and "k_linear_pack" not in names[1], names
