@@ -311,7 +311,8 @@ void plan_pack(const LinearArgs& a, const aol_tiler* in, const aol_tiler* out, c
 // The matrix-core form's layout and tables (appended to tab), or use = 0 when
 // it does not apply: more than kLinStageMaxIn pattern elements (smaller
 // patterns have the staged form, or keep too little of a product busy), no two
-// on one position and none reaching as far as an axis is long, a box that fits
+// on one position and none reaching as far as an axis is long, axes of at most
+// 2^30 (the kernel adds two coordinates in 32 bits), a box that fits
 // kLinBoxLds and is no longer than twice an axis, at most
 // kLinBoxSteps K-steps, weights within two int8 parts.
 void plan_box(const LinearArgs& a, const aol_tiler* in, const int16_t* weights, const int32_t* bias, int n_in,
@@ -325,7 +326,9 @@ void plan_box(const LinearArgs& a, const aol_tiler* in, const int16_t* weights, 
     if (m >= (1LL << 31)) return;
   }
   for (int d = 0; d < a.ra; ++d)
-    if (a.lo[d] <= -a.S[d] || a.hi[d] >= a.S[d]) return;
+    if (a.lo[d] <= -a.S[d] || a.hi[d] >= a.S[d] || a.S[d] > (1 << 30)) return;
+  for (int d = 0; d < a.ro; ++d)
+    if (a.So[d] > (1 << 30)) return;
   int32_t Ps[kLinRank][kLinRank];  // pavings, signed, nearest zero
   for (int d = 0; d < a.ra; ++d)
     for (int k = 0; k < a.rr; ++k) Ps[d][k] = (int64_t)a.P[d][k] * 2 > a.S[d] ? a.P[d][k] - a.S[d] : a.P[d][k];

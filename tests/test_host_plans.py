@@ -71,3 +71,14 @@ def rgb(p):
 print(json.dumps([rgb(1500), rgb(-2 ** 63)]))
 """)
     assert "k_linear_pack" in names[0] and "k_linear_pack" not in names[1], names
+
+
+def test_linear_matrix_core_form_axes(host):
+    """Axes above 2^30 stay off the matrix-core form, whose coordinates are sums of two in 32 bits."""
+    names = host(LINEAR + """
+def fir(n):
+    return kernel((n,), (4, 400), (64,), (n - 5,), [[0, 1]], [[1]], (4, 400, 8), [[1, 0], [0, 1], [0, 0]], [[0], [0], [1]], (8,))
+print(json.dumps([fir(2 ** 30), fir(2 ** 30 + 1), fir(2 ** 31 - 1)]))
+""")
+    assert "k_linear_box" in names[0], names
+    assert all("k_linear_box" not in n for n in names[1:]), names
