@@ -77,7 +77,7 @@ def test_linear_matrix_core_form_axes(host):
     """Axes above 2^30 stay off the matrix-core form, whose coordinates are sums of two in 32 bits."""
     names = host(LINEAR + """
 def fir(n):
-    return kernel((n,), (4, 400), (64,), (n - 5,), [[0, 1]], [[1]], (4, 400, 8), [[1, 0], [0, 1], [0, 0]], [[0], [0], [1]], (8,))
+    return kernel((n,), (16, 400), (64,), (n - 5,), [[0, 1]], [[1]], (16, 400, 8), [[1, 0], [0, 1], [0, 0]], [[0], [0], [1]], (8,))
 print(json.dumps([fir(2 ** 30), fir(2 ** 30 + 1), fir(2 ** 31 - 1)]))
 """)
     assert "k_linear_box" in names[0], names
