@@ -86,17 +86,24 @@ __device__ __forceinline__ void linear_points(const LinearArgs& a, const int (&r
   const lin_in_t in = (lin_in_t)a.in;
   const lin_out_t out = (lin_out_t)a.out;
 
-  for (int rl = xb + (int)threadIdx.x; rl < xe; rl += kLinThreads) {
+  // (coordinates and offsets are below 2^31, the sum of two below 2^32)
+  auto wrap = [](int c, int step, int S) {
+    uint32_t v = (uint32_t)c + (uint32_t)step;
+    if (v >= (uint32_t)S) v -= (uint32_t)S;
+    return (int)v;
+  };
+
+  for (uint32_t rl = (uint32_t)xb + threadIdx.x; rl < (uint32_t)xe; rl += kLinThreads) {
     bool inside = true, oinside = true;
     int flat = 0, oflat = 0;
 #pragma unroll
     for (int d = 0; d < kLinRank; ++d) {
       if (d < a.ra) {
-        inside = inside && b[d] + a.lo[d] >= 0 && b[d] + a.hi[d] < a.S[d];
+        inside = inside && b[d] >= -a.lo[d] && b[d] < a.S[d] - a.hi[d];
         flat += b[d] * a.st[d];
       }
       if (d < a.ro) {
-        oinside = oinside && ob[d] + a.olo[d] >= 0 && ob[d] + a.ohi[d] < a.So[d];
+        oinside = oinside && ob[d] >= -a.olo[d] && ob[d] < a.So[d] - a.ohi[d];
         oflat += ob[d] * a.sto[d];
       }
     }
@@ -104,11 +111,7 @@ __device__ __forceinline__ void linear_points(const LinearArgs& a, const int (&r
       int f = 0;
 #pragma unroll
       for (int d = 0; d < kLinRank; ++d) {
-        if (d < a.ra) {
-          int c = b[d] + ifd[d * n2 + i];  // both in [0, S): one subtraction wraps
-          if (c >= a.S[d]) c -= a.S[d];
-          f += c * a.st[d];
-        }
+        if (d < a.ra) f += wrap(b[d], ifd[d * n2 + i], a.S[d]) * a.st[d];  // both in [0, S)
       }
       return in[f];
     };
@@ -142,11 +145,7 @@ __device__ __forceinline__ void linear_points(const LinearArgs& a, const int (&r
         f = 0;
 #pragma unroll
         for (int d = 0; d < kLinRank; ++d) {
-          if (d < a.ro) {
-            int c = ob[d] + ofd[d * NOUT + j];
-            if (c >= a.So[d]) c -= a.So[d];
-            f += c * a.sto[d];
-          }
+          if (d < a.ro) f += wrap(ob[d], ofd[d * NOUT + j], a.So[d]) * a.sto[d];
         }
       }
       out[f] = (uint8_t)min(max(acc[j] >> 8, 0), 255);  // arithmetic shift: floor division by 256
@@ -154,14 +153,8 @@ __device__ __forceinline__ void linear_points(const LinearArgs& a, const int (&r
     // next point of the thread along the last repetition dimension
 #pragma unroll
     for (int d = 0; d < kLinRank; ++d) {
-      if (d < a.ra) {
-        b[d] += a.inc[d];
-        if (b[d] >= a.S[d]) b[d] -= a.S[d];
-      }
-      if (d < a.ro) {
-        ob[d] += a.oinc[d];
-        if (ob[d] >= a.So[d]) ob[d] -= a.So[d];
-      }
+      if (d < a.ra) b[d] = wrap(b[d], a.inc[d], a.S[d]);
+      if (d < a.ro) ob[d] = wrap(ob[d], a.oinc[d], a.So[d]);
     }
   }
 }
