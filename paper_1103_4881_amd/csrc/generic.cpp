@@ -412,7 +412,7 @@ static aol_status wsum_create(const aol_tiler* in, const aol_tiler* out, const f
       for (int k = 0; k < a.rr; ++k) most += (a.Ps[d][k] < 0 ? -a.Ps[d][k] : a.Ps[d][k]) * (R[k] + 63);
       if (most >= INT32_MAX) a.small = 0;
     }
-    // blocks of 64 x 4 points (fewer blocks than points, so under 2^31)
+    // blocks of 64 x 4 points (fewer blocks than points, so under 2^31; wsum_launch cuts them to grids)
     blocks /= a.nb_loop;
     a.nb_loop = (int32_t)((R[k_loop] + 3) / 4);
     blocks *= a.nb_loop;

@@ -148,7 +148,7 @@ __global__ __launch_bounds__(256) void k_wsum(WsumArgs a) {
   // block -> (lane block, loop block, other repetition indices), uniform and
   // in 32 bits (fewer than 2^31 blocks); arrays indexed by unrolled
   // constants only, so they stay in scalar registers
-  uint32_t blk = blockIdx.x;
+  uint32_t blk = blockIdx.x + a.first;
   uint32_t q = wsum_div(blk, (uint32_t)a.nb_lane, a.mg_lane);
   const int bl = (int)(blk - q * (uint32_t)a.nb_lane);
   blk = q;
@@ -459,8 +459,16 @@ hipError_t wsum_launch(const WsumArgs& a, int64_t blocks, hipStream_t stream) {
   // the box, one spill slot per lane, then the row offsets; or the transposed tile
   size_t lds = a.use_box ? (size_t)(a.box_elems + 64 + a.box_rows) * 4 : 0;
   if (a.transpose) lds = std::max(lds, (size_t)64 * (4 * (a.use_box ? a.points : 1) + 1) * 4);
-  hipLaunchKernelGGL(wsum_pick(a), dim3((unsigned)blocks), dim3(256), lds, stream, a);
-  return hipGetLastError();
+  // a grid holds fewer than 2^32 threads
+  constexpr int64_t kMaxGrid = 1 << 23;
+  WsumArgs part = a;
+  for (int64_t first = 0; first < blocks; first += kMaxGrid) {
+    part.first = (uint32_t)first;
+    hipLaunchKernelGGL(wsum_pick(a), dim3((unsigned)std::min(kMaxGrid, blocks - first)), dim3(256), lds, stream, part);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace aol

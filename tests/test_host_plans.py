@@ -82,3 +82,25 @@ print(json.dumps([fir(2 ** 30), fir(2 ** 30 + 1), fir(2 ** 31 - 1)]))
 """)
     assert "k_linear_box" in names[0], names
     assert all("k_linear_box" not in n for n in names[1:]), names
+
+
+@pytest.mark.parametrize("rep,paving", [((8192, 8192, 4), [[1, 0, 9], [0, 1, 3], [0, 0, 1]]),
+                                        ((2 ** 24 + 9, 2, 1), [[1, 0, 0], [3, 0, 0], [0, 1, 0]])])
+def test_weighted_sum_grids(host, rep, paving):
+    """Repetition spaces of more blocks than a grid holds (2^32 threads): cut into several launches that
+    together hold every block, plan and one-shot form."""
+    counts = host(f"""
+rep, paving = {rep}, {paving}
+tin = aol.make_tiler((64, 70, 70), rep, (9,), (0, 0, 0), paving, [[1], [0], [0]])
+plan = aol.aol_wsum_plan_create(tin, aol.identity_out_tiler(rep), np.ones(9))
+n = []
+for run in (lambda: aol.aol_wsum_run(plan, BUF, 2 * BUF, 0),
+            lambda: aol.aol_weighted_sum_f32(tin, aol.identity_out_tiler(rep), np.ones(9), BUF, 2 * BUF, 0)):
+    stub.stub_reset()
+    run()
+    assert all(g * b < 2 ** 32 for _, g, b in launches())
+    n.append(sum(g for _, g, _ in launches()))
+print(json.dumps(n))
+""")
+    points = rep[0] * rep[1] * rep[2]
+    assert counts[0] == counts[1] >= points // (64 * 64), counts
