@@ -409,13 +409,17 @@ static aol_status wsum_create(const aol_tiler* in, const aol_tiler* out, const f
     a.small = 1;
     for (int d = 0; d < a.ra; ++d) {
       int64_t most = a.S[d];
-      for (int k = 0; k < a.rr; ++k) most += (a.Ps[d][k] < 0 ? -a.Ps[d][k] : a.Ps[d][k]) * (R[k] + 63);
+      for (int k = 0; k < a.rr; ++k) most += (a.Ps[d][k] < 0 ? -a.Ps[d][k] : a.Ps[d][k]) * (R[k] + 255);
       if (most >= INT32_MAX) a.small = 0;
     }
-    // blocks of 64 x 4 points (fewer blocks than points, so under 2^31; wsum_launch cuts them to grids)
-    blocks /= a.nb_loop;
-    a.nb_loop = (int32_t)((R[k_loop] + 3) / 4);
-    blocks *= a.nb_loop;
+    // blocks of 256 points, up to 64 of them lanes (fewer blocks than points,
+    // so under 2^31; wsum_launch cuts them to grids)
+    while (a.lane_log2 < 6 && 1 << a.lane_log2 < R[k_lane]) ++a.lane_log2;
+    const int64_t bl = 1 << a.lane_log2, bj = 256 >> a.lane_log2;
+    blocks /= (int64_t)a.nb_lane * a.nb_loop;
+    a.nb_lane = (int32_t)((R[k_lane] + bl - 1) / bl);
+    a.nb_loop = (int32_t)((R[k_loop] + bj - 1) / bj);
+    blocks *= (int64_t)a.nb_lane * a.nb_loop;
   }
   a.mg_lane = magic(a.nb_lane);
   a.mg_loop = magic(a.nb_loop);

@@ -29,7 +29,8 @@ struct WsumArgs {
   int32_t k_lane, k_loop;                // repetition dims along lanes / along each thread's loop
   int32_t points;                        // points per thread along k_loop
   int32_t small;                         // the points' unwrapped base indices, from Ps, fit 32 bits
-  int32_t nb_lane, nb_loop;              // blocks along k_lane (64 wide) / k_loop
+  int32_t lane_log2;                     // direct form: a block's points along k_lane (2^lane_log2, of 256 in all)
+  int32_t nb_lane, nb_loop;              // blocks along k_lane / k_loop
   uint32_t first;                        // the launch's first block (a large one is cut)
   uint32_t mg_lane, mg_loop, mg_R[kWsumMaxRank];  // floor(2^32 / divisor) + 1 of nb_lane, nb_loop, R
   int32_t other[kWsumMaxRank];

@@ -6,8 +6,8 @@
 // single result to B[(o' + P'.r) mod S']. Here the elementary task is
 // y = sum_i w[i] * pattern[i].
 //
-// Work mapping: a workgroup covers a block of two repetition dimensions, 64
-// points of the first along its lanes, with every other repetition index
+// Work mapping: a workgroup covers a block of two repetition dimensions, up to
+// 64 points of the first along its lanes, with every other repetition index
 // fixed. Lanes run along the dimension whose paving column walks the input's
 // contiguous axis (the gathers of one pattern element are then adjacent
 // addresses). A pattern that stays inside the array uses constant flat
@@ -15,11 +15,14 @@
 // output's contiguous dimension is the second one, results go through a
 // transposed LDS tile so that stores are contiguous too.
 //
-// Direct form: one point per thread, four along the second dimension per
-// workgroup. Bound by the latency of a thread's gathers (eight in flight), so
-// points of one thread only lengthen the chain: 10 x 768 x 372 inputs, 25
-// elements: 96 us with 16 points, 29 with four, 20 with one; 57 x 951 x 412, 16
-// elements: 82, 65, 62 us.
+// Direct form: one point per thread, 256 per workgroup. Bound by the latency of
+// a thread's gathers (eight in flight), so points of one thread only lengthen
+// the chain: 10 x 768 x 372 inputs, 25 elements: 96 us with 16 points, 29 with
+// four, 20 with one; 57 x 951 x 412, 16 elements: 82, 65, 62 us. A first
+// dimension of fewer than 64 points takes as many lanes as the next power of
+// two, and the block more of the second: 2^21 points, nine elements, sheared,
+// first dimension of 2, 8 and 32 points: 496, 127 and 51 us with 64 lanes, 19,
+// 19 and 36 so.
 //
 // Staged form (BOX): when the input elements a block of points reads lie in a
 // box small enough for LDS, the workgroup first loads that box (rows along
@@ -133,17 +136,20 @@ __device__ __forceinline__ void wsum_box_classes(const WsumArgs& a, const float*
   }
 }
 
-// PT: points per thread along the loop dimension (a block is 64 x 4*PT
-// points).
+// PT: points per thread along the loop dimension (a block of the staged form is
+// 64 x 4*PT points).
 // EM: the widest class of shared reads (0: one read per pattern element).
 template <bool BOX, int EM, int PT>
 __global__ __launch_bounds__(256) void k_wsum(WsumArgs a) {
-  constexpr int BJ = 4 * PT;  // block extent along the loop dimension
-  constexpr int TP = BJ + 1;  // pitch of the transposed tile (in the box's place once its sums are done)
+  // Block extents along the lane and the loop dimension. Direct form: as many
+  // lanes as the lane dimension fills, so that a short one leaves no thread idle.
+  const int ll = BOX ? 6 : a.lane_log2, BL = BOX ? 64 : 1 << ll, BJ = BOX ? 4 * PT : 256 >> ll;
+  const int TP = BJ + 1;  // pitch of the transposed tile (in the box's place once its sums are done)
   extern __shared__ __attribute__((aligned(16))) float box[];
   float* tile = box;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & (BL - 1);
+  // the thread's first point along the loop dimension, in points of PT (staged form: uniform in a wave)
+  const int wave = BOX ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : (int)(threadIdx.x >> ll);
 
   // block -> (lane block, loop block, other repetition indices), uniform and
   // in 32 bits (fewer than 2^31 blocks); arrays indexed by unrolled
@@ -164,12 +170,12 @@ __global__ __launch_bounds__(256) void k_wsum(WsumArgs a) {
       rc[k] = (int)(blk - q * (uint32_t)a.R[k]);
       blk = q;
     } else if (k == a.k_lane) {
-      rc[k] = bl * 64;
+      rc[k] = bl * BL;
     } else if (k == a.k_loop) {
       rc[k] = bp * BJ;
     }
   }
-  const int r_lane = bl * 64 + lane;
+  const int r_lane = bl * BL + lane;
   const int r_loop0 = bp * BJ + wave * PT;
   int64_t r[kWsumMaxRank];  // this thread's first point
 #pragma unroll
@@ -416,18 +422,19 @@ __global__ __launch_bounds__(256) void k_wsum(WsumArgs a) {
     uint32_t rowbase = 0;
     for (int k = 0; k < a.rr; ++k)
       if (k != a.k_lane && k != a.k_loop) rowbase += (uint32_t)r[k] * (uint32_t)a.ostr_rep[k];
-    // A row of the tile is BJ points: 64 / BJ rows per wave (with BJ = 32 the
-    // halves take rows r and r + 32, 33 * 32 = 32 mod 64 banks apart: no
-    // conflict).
-    constexpr int HALVES = 64 / BJ;
-    const int col = lane % BJ, half = lane / BJ;
-    const int rl = bp * BJ + col;
+    // A row of the tile is BJ points: with BJ = 32 the halves of a wave take
+    // rows r and r + 32 (33 * 32 = 32 mod 64 banks apart: no conflict).
     const uint32_t sl = (uint32_t)a.ostr_rep[a.k_lane];
-    const int row0 = wave + half * (64 / HALVES);
-    uint32_t of = rowbase + (uint32_t)(bl * 64 + row0) * sl + (uint32_t)rl * (uint32_t)a.ostr_rep[a.k_loop];
+    constexpr int ROWS = 4 * PT;  // staged form: a wave takes these rows of its half, four apart
+    const int col = BOX ? lane % (4 * PT) : (int)(threadIdx.x & (BJ - 1));
+    const int row0 = BOX ? wave + lane / (4 * PT) * ROWS : (int)(threadIdx.x >> (8 - ll));  // direct form: one row each
+    const int rl = bp * BJ + col;
+    uint32_t of = rowbase + (uint32_t)(bl * BL + row0) * sl + (uint32_t)rl * (uint32_t)a.ostr_rep[a.k_loop];
     const bool col_ok = rl < a.R[a.k_loop];
-    for (int row = row0; row < row0 + 64 / HALVES; row += 4, of += 4 * sl) {
-      if (col_ok && bl * 64 + row < a.R[a.k_lane]) ((gout_t)a.out)[of] = tile[row * TP + col];
+#pragma unroll
+    for (int i = 0; i < ROWS; i += 4, of += 4 * sl) {
+      const int row = row0 + i;
+      if (col_ok && bl * BL + row < a.R[a.k_lane]) ((gout_t)a.out)[of] = tile[row * TP + col];
     }
   }
 }
@@ -458,7 +465,8 @@ hipError_t wsum_prepare() {
 hipError_t wsum_launch(const WsumArgs& a, int64_t blocks, hipStream_t stream) {
   // the box, one spill slot per lane, then the row offsets; or the transposed tile
   size_t lds = a.use_box ? (size_t)(a.box_elems + 64 + a.box_rows) * 4 : 0;
-  if (a.transpose) lds = std::max(lds, (size_t)64 * (4 * (a.use_box ? a.points : 1) + 1) * 4);
+  if (a.transpose)
+    lds = std::max(lds, a.use_box ? (size_t)64 * (4 * a.points + 1) * 4 : ((size_t)256 + ((size_t)1 << a.lane_log2)) * 4);
   // a grid holds fewer than 2^32 threads
   constexpr int64_t kMaxGrid = 1 << 23;
   WsumArgs part = a;

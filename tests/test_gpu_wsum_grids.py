@@ -1,5 +1,7 @@
-"""GPU parity of weighted sums of more blocks than one grid holds: the launch is cut, and every piece
-computes its own blocks. |y - y64| <= 4 * 2^-24 * sum_i |w_i x_i| (three fused multiply-adds)."""
+"""GPU parity of weighted sums at the edges of their blocks and grids. Short first dimensions of the
+direct form (sheared tilers), around the powers of two that its lanes take and the rest of a block's 256
+points, with identity and permuted outputs. More blocks than one grid holds: the launch is cut, and every
+piece computes its own blocks; |y - y64| <= 4 * 2^-24 * sum_i |w_i x_i| (three fused multiply-adds)."""
 
 import numpy as np
 import pytest
@@ -9,6 +11,7 @@ import synthgen
 import torch
 
 import paper_1103_4881_amd as aol  # a missing library fails the suite (no skip)
+from tests.test_gpu_wsum_forms import _case
 
 pytestmark = pytest.mark.gpu
 
@@ -33,3 +36,14 @@ def test_more_blocks_than_a_grid(fit):
         want += v
         mag += v.abs()
     assert ((y[:, :, 0].double() - want).abs() <= 4 * 2.0 ** -24 * mag).all()
+
+
+@pytest.mark.parametrize("lane", [1, 2, 3, 4, 5, 8, 9, 16, 17, 32, 33])
+@pytest.mark.parametrize("pat", [(3, 1), (2, 5)])
+def test_direct_short_lanes(lane, pat):
+    for loop in (1, 256 // lane - 1, 256 // lane + 1, 300):
+        shape = (lane + 40, 2 * loop + 30, 3 * lane + 350)
+        paving = [[1, 0, 9], [0, 2, 7], [0, 3, 1]]  # the lane dimension walks all three axes: no box fits
+        for flip in (False, True):
+            _case(shape, (3, loop, lane), pat, (5, 1, 2), paving, [[1, 0], [0, 0], [0, -50]], flip)
+        _case((lane + 40, 2 * loop + 30), (loop, lane), pat, (5, 1), [[5, 1], [2, 1]], [[1, 0], [0, -50]])

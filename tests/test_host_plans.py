@@ -104,3 +104,20 @@ print(json.dumps(n))
 """)
     points = rep[0] * rep[1] * rep[2]
     assert counts[0] == counts[1] >= points // (64 * 64), counts
+
+
+def test_weighted_sum_short_lane_dimension(host):
+    """The direct form's threads nearly all have a point, however short the dimension of its lanes."""
+    got = host("""
+got = []
+for lane in (2, 3, 4, 8, 16, 32, 64):
+    rep = (1 << 18, lane)
+    tin = aol.make_tiler(((1 << 18) + 70, lane), rep, (9,), (0, 0), [[1, 7], [0, 1]], [[1], [0]])
+    plan = aol.aol_wsum_plan_create(tin, aol.identity_out_tiler(rep), np.ones(9))
+    stub.stub_reset()
+    aol.aol_wsum_run(plan, BUF, 2 * BUF, 0)
+    got.append([launches()[0][0], sum(g * b for _, g, b in launches()) / (rep[0] * rep[1])])
+print(json.dumps(got))
+""")
+    for name, threads_per_point in got:
+        assert "k_wsumILb0E" in name and threads_per_point <= 1.4, got
