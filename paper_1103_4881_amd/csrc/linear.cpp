@@ -308,13 +308,51 @@ void plan_pack(const LinearArgs& a, const aol_tiler* in, const aol_tiler* out, c
   if (blocks >= (1LL << 24)) p.inst = 0;
 }
 
+// Whether the matrix-core form is the faster one: times in us estimated for it
+// and for the point-by-point form, each the longer of what all its workgroups
+// take on the whole device and of one workgroup's chain. Fitted to 2,753
+// plans of 3,840 to 1,000,000 points (8 % off in the median): a product's K-step
+// on chunks at any byte costs about as much as five pairs of elements point by
+// point, so patterns with few elements per chunk and few outputs are slower as
+// products (1000 x 1000 points, 33 x 1 elements, one output: nine K-steps 71 us,
+// point by point 33; 6 x 6 elements, four outputs: 29 and 38; 17 x 17, nine
+// outputs at 1/8: 59 and 239). Chosen with a tenth to spare: of those plans 19 are
+// slower than the other form (9 % at most), 63 miss a gain (1.4 times at most).
+bool box_pays(const LinearArgs& a, const LinearBox& b, const int32_t (&Ps)[kLinRank][kLinRank], int64_t blocks,
+              int chunks) {
+  const int last = a.rr - 1;
+  const double kb = b.lds_bytes / 1024.0, mb = blocks * 256 / 1e6;
+  const double step = (b.align < 8 ? 6.2 : 0.0) + (b.split ? 1.0 : 0.0);
+  const double box = std::max({mb * (12.3 + 1.7 * kb + b.steps * step + 0.2 * a.n_out), mb * 29.0,
+                               7.3 + 0.45 * b.steps + 0.1 * std::max(0.0, kb - 16)});
+  // point by point: a workgroup per row, 256 points of it at a time; lanes `stride` bytes apart
+  const int64_t rows = a.nrep / a.R[last], turns = (a.R[last] + kLinThreads - 1) / kLinThreads;
+  if (rows >= (1LL << 24)) return true;  // (more rows than a grid holds)
+  const double mp = (double)rows * turns * kLinThreads / 1e6;
+  int64_t stride = 0;
+  bool wraps = false;  // some point's pattern leaves the array: its wave computes every address
+  for (int d = 0; d < a.ra; ++d) {
+    stride += std::abs((int64_t)Ps[d][last]) * a.st[d];
+    int64_t lo = (int64_t)a.o[d] + a.lo[d], hi = (int64_t)a.o[d] + a.hi[d];
+    for (int k = 0; k < a.rr; ++k) (Ps[d][k] < 0 ? lo : hi) += (int64_t)Ps[d][k] * (a.R[k] - 1);
+    wraps = wraps || lo < 0 || hi >= a.S[d];
+  }
+  const double far = (double)std::min<int64_t>(std::max<int64_t>(stride - 1, 0), 15);
+  const double inner = 0.05 + 0.0022 * a.nout_pad, edge = 0.335 + 0.011 * a.nout_pad;
+  const double points =
+      std::max(mp * (a.n_pairs * (1.24 + 0.073 * a.nout_pad) + chunks * (0.09 + 0.24 * far) + 0.28 * a.nout_pad),
+               6.0 + a.n_pairs * ((turns - 1) * inner + (wraps ? edge : inner)));
+  return box < 0.9 * points;
+}
+
 // The matrix-core form's layout and tables (appended to tab), or use = 0 when
 // it does not apply: more than kLinStageMaxIn pattern elements (smaller
 // patterns have the staged form, or keep too little of a product busy), no two
 // on one position and none reaching as far as an axis is long, axes of at most
 // 2^30 (the kernel adds two coordinates in 32 bits), a box that fits
 // kLinBoxLds and is no longer than twice an axis, at most
-// kLinBoxSteps K-steps, weights within two int8 parts.
+// kLinBoxSteps K-steps, weights within two int8 parts, and faster than point by
+// point.
 void plan_box(const LinearArgs& a, const aol_tiler* in, const int16_t* weights, const int32_t* bias, int n_in,
               int n_out, LinearBox& b, std::vector<int32_t>& tab) {
   memset(&b, 0, sizeof b);
@@ -418,6 +456,21 @@ void plan_box(const LinearArgs& a, const aol_tiler* in, const int16_t* weights, 
   // (a chunk may reach 15 bytes past the box: weight zero there)
   b.lds_bytes = (int32_t)((b.lds_box + best + 16 + 15) / 16 * 16);
   if (b.lds_bytes > kLinBoxLds) return;
+  int64_t blocks = 1, terms = 0;
+  for (int k = 0; k < a.rr; ++k) {
+    const int e = k == last ? kLinBoxX : k == kj ? kLinBoxY : 1;
+    b.nb[k] = (a.R[k] + e - 1) / e;
+    b.mg_nb[k] = magic((uint32_t)b.nb[k]);
+    blocks *= b.nb[k];
+    terms += (int64_t)b.nb[k] * (a.ra + a.ro);
+  }
+  if (blocks >= (1LL << 24) || terms > kLinCoordTable) return;
+  b.align = 16;
+  for (int64_t v : chunks)
+    while (v % b.align) b.align /= 2;
+  while (b.lstep % b.align || b.jstep % b.align) b.align /= 2;
+  b.split = split ? 1 : 0;
+  if (!box_pays(a, b, Ps, blocks, (int)chunks.size())) return;
   // weights in lane order: lane (g, m): output m, bytes of chunk 4 k + g
   while (tab.size() % 4) tab.push_back(0);
   b.t_w = (int32_t)tab.size();
@@ -442,15 +495,6 @@ void plan_box(const LinearArgs& a, const aol_tiler* in, const int16_t* weights, 
     for (int i = 0; j < n_out && i < n_in; ++i) sum += weights[(size_t)j * n_in + i];
     tab.push_back((int32_t)((j < n_out && bias ? bias[j] : 0) + 128 + 128 * sum));
   }
-  int64_t blocks = 1, terms = 0;
-  for (int k = 0; k < a.rr; ++k) {
-    const int e = k == last ? kLinBoxX : k == kj ? kLinBoxY : 1;
-    b.nb[k] = (a.R[k] + e - 1) / e;
-    b.mg_nb[k] = magic((uint32_t)b.nb[k]);
-    blocks *= b.nb[k];
-    terms += (int64_t)b.nb[k] * (a.ra + a.ro);
-  }
-  if (blocks >= (1LL << 24) || terms > kLinCoordTable) return;
   for (int k = 0; k < a.rr; ++k) {
     const int64_t e = k == last ? kLinBoxX : k == kj ? kLinBoxY : 1;
     b.t_org[k] = (int32_t)tab.size();
@@ -472,11 +516,6 @@ void plan_box(const LinearArgs& a, const aol_tiler* in, const int16_t* weights, 
     if (std::abs((int64_t)b.Pl[d]) * (kLinBoxX - 1) + std::abs((int64_t)b.Pj[d]) * (kLinBoxY - 1) > a.So[d]) return;
   }
   b.mg_nch = magic((uint32_t)b.nch);
-  b.align = 16;
-  for (int64_t v : chunks)
-    while (v % b.align) b.align /= 2;
-  while (b.lstep % b.align || b.jstep % b.align) b.align /= 2;
-  b.split = split ? 1 : 0;
   b.use = 1;
 }
 

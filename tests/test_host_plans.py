@@ -121,3 +121,18 @@ print(json.dumps(got))
 """)
     for name, threads_per_point in got:
         assert "k_wsumILb0E" in name and threads_per_point <= 1.4, got
+
+
+def test_linear_matrix_core_form_only_where_it_pays(host):
+    """Dense windows run on the matrix cores; patterns with few elements in a 16-byte chunk and few
+    outputs point by point (as products 2.1 to 2.5 times slower)."""
+    names = host(LINEAR + """
+def window(n, k, d, n_out, value, q=1):
+    return kernel((n * q, n * q), (n, n), k, (0, 0), [[q, 0], [0, q]], [[d[0], 0], [0, d[1]]],
+                  (n, n, n_out), [[1, 0], [0, 1], [0, 0]], [[0], [0], [1]], (n_out,), value)
+print(json.dumps([[window(300, (17, 17), (1, 1), 9, 1, 8), window(1000, (12, 12), (1, 1), 1, 1), window(60, (8, 8), (1, 1), 4, 300)],
+                  [window(1000, (33, 1), (1, 1), 1, 1), window(1000, (1, 33), (3, 20), 2, 300), window(1000, (7, 7), (3, 20), 1, 300),
+                   window(60, (8, 8), (1, 1), 1, 1, 16)]]))
+""")
+    assert all("k_linear_box" in n for n in names[0]), names
+    assert all("k_linear_box" not in n for n in names[1]), names
