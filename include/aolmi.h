@@ -350,8 +350,8 @@ aol_status aol_batch_buffers_create(aol_batch_plan* plan, const void* const* d_i
 aol_status aol_batch_run_buffers(aol_batch_plan* plan, const aol_buffer_set* set, hipStream_t stream);
 aol_status aol_batch_buffers_destroy(aol_buffer_set* set);
 
-/* Times schedule candidates on the buffers last set: first one segment
- * length for every stream (16..128 repetitions; with streams of 4 GiB or more
+/* Times schedule candidates on the buffers last set: first the default, then one
+ * segment length for every stream (16..128 repetitions; with streams of 4 GiB or more
  * also the column-band LDS budget, 150 or 76 KiB); then, classes with the most
  * input first, each stream class's own segment length (16..128; a class: the
  * two ratios and the width class up to 640, 1280, 1920 pixels or wider) with

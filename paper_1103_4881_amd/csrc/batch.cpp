@@ -822,10 +822,11 @@ aol_status aol_autotune(aol_batch_plan* plan, hipStream_t stream) {
     }
     return st == AOL_OK;
   };
-  // 1. one segment length and LDS budget (column band) for every stream
+  // 1. the default (its segments may be shorter than any below), then one segment
+  // length and LDS budget (column band) for every stream
   const int segs[] = {16, 32, 64, 128};
   const int budgets[] = {150 * 1024, 76 * 1024};
-  bool go = true;
+  bool go = trial(Schedule());
   for (int budget : budgets)
     for (int seg : segs) {
       if (plan->strips && budget != budgets[0]) continue;  // the strip kernel has no column band

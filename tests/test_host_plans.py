@@ -136,3 +136,26 @@ print(json.dumps([[window(300, (17, 17), (1, 1), 9, 1, 8), window(1000, (12, 12)
 """)
     assert all("k_linear_box" in n for n in names[0]), names
     assert all("k_linear_box" not in n for n in names[1]), names
+
+
+TUNE = """
+stub.stub_elapsed.argtypes = [ctypes.POINTER(ctypes.c_float), ctypes.c_int]
+f = aol.Polyphase(3, 8, synthgen.design_taps(3, 8, 11))
+def tuned(cache, times):
+    plan = aol.BatchPlan([(480, 640, f, f)] * 5, tune_cache=cache)
+    aol.aol_batch_set_pointers(plan._h, aol._ptrs([BUF] * 5), aol._ptrs([BUF] * 5), 0)
+    stub.stub_elapsed((ctypes.c_float * len(times))(*times), len(times))
+    aol.aol_autotune(plan._h, 0)
+    return json.loads(plan.schedule())
+"""
+
+
+def test_autotune_times_the_default(host, tmp_path):
+    """A tuned batch is no slower than an untuned one: the default schedule is among the candidates (here
+    the first one timed is the fastest)."""
+    sched, again = host(TUNE + f"""
+cache = {str(tmp_path / "tune.txt")!r}
+sched = tuned(cache, [0.5] * 3)
+print(json.dumps([sched, json.loads(aol.BatchPlan([(480, 640, f, f)] * 5, tune_cache=cache).schedule())]))
+""")
+    assert sched["seg"] == 0 and not any(sched["class_segs"]) and again == sched, (sched, again)
