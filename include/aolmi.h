@@ -356,7 +356,7 @@ aol_status aol_batch_buffers_destroy(aol_buffer_set* set);
  * input first, each stream class's own segment length (16..128; a class: the
  * two ratios and the width class up to 640, 1280, 1920 pixels or wider) with
  * the others held. Keeps the fastest and appends
- * it to the tuning cache (keyed by the device architecture, the precision and
+ * it to the tuning cache (keyed by the device architecture, the precision, the kernel and
  * the streams' sizes and filters). Synchronises the stream (not a run call);
  * results are unchanged. */
 aol_status aol_autotune(aol_batch_plan* plan, hipStream_t stream);

@@ -444,8 +444,9 @@ static aol_status batch_pointer_list(const aol_batch_plan* plan, const void* con
   return AOL_OK;
 }
 
-// Key of a batch for the tuning cache: device architecture, precision and
-// every stream's geometry and filter.
+// Key of a batch for the tuning cache: device architecture, precision, every
+// stream's geometry and filter, and the kernel (what is fast on one is not on
+// another: lines tuned for the band kernel keep the plain key).
 static std::string batch_key(const aol_batch_plan* bp) {
   std::string k;
   hipDeviceProp_t prop;
@@ -473,7 +474,7 @@ static std::string batch_key(const aol_batch_plan* bp) {
   }
   char buf[32];
   snprintf(buf, sizeof buf, "|%016llx", (unsigned long long)h);
-  return k + buf;
+  return k + buf + (bp->strips ? "|strip" : "");
 }
 
 // Tiny line-oriented cache: "key seg budget n_classes class_seg... part_weight"
@@ -610,13 +611,13 @@ aol_status aol_batch_plan_create(int32_t n_streams, const aol_stream_desc* strea
       bp->cls_bytes[j] += bp->desc[i].height * bp->desc[i].width;
     }
   }
+  st = batch_strips(bp, rep);
   bp->key = batch_key(bp);
   Schedule sc;
   if (tune_cache) {
     bp->cache_path = tune_cache;
     cache_lookup(bp->cache_path, bp->key, &sc);
   }
-  st = batch_strips(bp, rep);
   // capacity: the most units any schedule can make (bands and segments of 16 repetitions)
   for (aol_batch_plan::Part& P : bp->parts) {
     for (int i : P.ids) {

@@ -159,3 +159,22 @@ sched = tuned(cache, [0.5] * 3)
 print(json.dumps([sched, json.loads(aol.BatchPlan([(480, 640, f, f)] * 5, tune_cache=cache).schedule())]))
 """)
     assert sched["seg"] == 0 and not any(sched["class_segs"]) and again == sched, (sched, again)
+
+
+def test_tuning_cache_names_the_kernel(host, tmp_path):
+    """A line tuned for the column-band kernel (the plain key) is not applied to the strip kernel, nor the
+    other way round (a batch with a stream beyond the strip kernel runs the column-band kernel)."""
+    got = host(TUNE + f"""
+cache = {str(tmp_path / "tune.txt")!r}
+tuned(cache, [0.5] * 6 + [0.1] * 3)
+key = open(cache).read().split()[0]
+plain = key[:-len("|strip")] if key.endswith("|strip") else key
+seg = lambda shapes, **kw: json.loads(aol.BatchPlan([(h, w, f, f, ip, 0) for h, w, ip in shapes], **kw).schedule())["seg"]
+got = [seg([(480, 640, 640)] * 5, tune_cache=cache)]
+open(cache, "w").write(plain + " 128 153600 0 1000\\n")
+got += [seg([(480, 640, 640)] * 5, tune_cache=cache), seg([(480, 640, 1 << 24)] * 5, tune_cache=cache)]
+open(cache, "w").write(plain + "|strip 64 153600 0 1000\\n")
+got += [seg([(480, 640, 640)] * 5, tune_cache=cache), seg([(480, 640, 1 << 24)] * 5, tune_cache=cache)]
+print(json.dumps(got))
+""")
+    assert got == [32, 0, 128, 64, 0], got
