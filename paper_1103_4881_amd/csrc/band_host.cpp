@@ -37,7 +37,8 @@ aol_status build_filter_bands(const FilterHost& hf, const FilterHost& vf, int el
     span = std::max(span, 16 * m - E * vb.chunk0[lb] - 16 * per * vb.q);
   }
   const int ring = (span + 16 + 15) / 16 * 16;  // whole steps of 16 lines
-  std::vector<uint32_t> vtab(2 * kBandVBlocks);
+  std::vector<uint32_t>& vtab = out.vtab;
+  vtab.resize(2 * kBandVBlocks);
   for (int B = 0; B < kBandVBlocks; ++B) {
     const int per = B / vb.nblk, lb = B % vb.nblk;
     const int c0 = vb.chunk0[lb] + per * (vb.q * 16 / E);  // chunks of E intermediate lines
@@ -45,18 +46,24 @@ aol_status build_filter_bands(const FilterHost& hf, const FilterHost& vf, int el
               ((uint32_t)vb.nk[lb] << 29);
     vtab[kBandVBlocks + B] = (uint32_t)(vb.wend[lb] + 16 * per * vb.q);
   }
-  if ((st = out.d_vtab.upload(vtab.data(), vtab.size() * sizeof(uint32_t)))) return st;
   out.elem = elem;
   out.hb = hb;
   out.vb = vb;
   out.ring = ring;
   out.split = hb.split || vb.split;
   out.kmax = std::max(hb.kmax, vb.kmax);
-  if ((st = out.d_hb.upload(&hb, sizeof hb))) return st;
-  if ((st = out.d_vb.upload(&vb, sizeof vb))) return st;
-  if ((st = out.d_hfrag.upload(hfr.data(), hfr.size()))) return st;
-  if ((st = out.d_vfrag.upload(vfr.data(), vfr.size()))) return st;
+  out.hfrag = std::move(hfr);
+  out.vfrag = std::move(vfr);
   return AOL_OK;
+}
+
+aol_status upload_filter_bands(FilterBands& fb) {
+  aol_status st = fb.d_vtab.upload(fb.vtab.data(), fb.vtab.size() * sizeof(uint32_t));
+  if (!st) st = fb.d_hb.upload(&fb.hb, sizeof fb.hb);
+  if (!st) st = fb.d_vb.upload(&fb.vb, sizeof fb.vb);
+  if (!st) st = fb.d_hfrag.upload(fb.hfrag.data(), fb.hfrag.size());
+  if (!st) st = fb.d_vfrag.upload(fb.vfrag.data(), fb.vfrag.size());
+  return st;
 }
 
 // LDS layout of one stream: two staging buffers of xbuf bytes at offset 0,

@@ -9,14 +9,17 @@
 
 namespace aol {
 
-// One filter pair's device tables for the band kernel: one period (16
-// repetitions) of each axis, coefficient operands in lane order.
+// One filter pair's tables for the band kernel: one period (16 repetitions) of
+// each axis, coefficient operands in lane order, on the host and (once
+// uploaded) on the device.
 struct FilterBands {
   int elem = kU8;
   AxisBand hb{}, vb{};
   int ring = 0;       // intermediate lines the vertical pass needs kept (a multiple of 16)
   int kmax = 0;       // largest K-step count of a block of either axis
   bool split = false;
+  std::vector<uint8_t> hfrag, vfrag;
+  std::vector<uint32_t> vtab;
   DeviceBuf d_hb, d_vb, d_hfrag, d_vfrag;
   // Vertical block table, copied into LDS with the coefficients: entry B
   // (bits 0-15: ring line of the block's first chunk; 16-23: first
@@ -28,6 +31,7 @@ struct FilterBands {
 constexpr int kBandVBlocks = 64;  // vertical blocks per unit at most (one per lane)
 
 aol_status build_filter_bands(const FilterHost& hf, const FilterHost& vf, int elem, bool force_split, FilterBands& out);
+aol_status upload_filter_bands(FilterBands& fb);  // before build_band_stream, for launches of the band kernel
 
 // Descriptor of one plane or stream of size h x w for the band kernel.
 // xreps = 0 picks the widest column band (whole periods) whose LDS fits

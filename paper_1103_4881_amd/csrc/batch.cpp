@@ -583,6 +583,7 @@ aol_status aol_batch_plan_create(int32_t n_streams, const aol_stream_desc* strea
   bp->bands.resize(rep.size());
   for (size_t g = 0; g < rep.size(); ++g) {
     st = build_filter_bands(bp->hf[rep[g]], bp->vf[rep[g]], bp->elem, false, bp->bands[g]);
+    if (!st) st = upload_filter_bands(bp->bands[g]);
     if (st) {
       delete bp;
       return st;

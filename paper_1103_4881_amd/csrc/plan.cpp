@@ -392,6 +392,31 @@ static aol_status plan_build_band(aol_plan* pl, int xreps, int seg) {
   FilterBands fb;
   aol_status st = build_filter_bands(pl->hf, pl->vf, pl->elem, false, fb);
   if (st) return st == AOL_ERR_UNSUPPORTED ? AOL_OK : st;
+  if (pl->strips.cls < 0) {
+    if ((st = build_strip_tables(pl->hf, pl->vf, pl->elem, pl->strips))) return st;
+    pl->sedges = false;
+    for (int i = 0; i < pl->n_planes && pl->strips.cls >= 0; ++i) {
+      const aol_plane_desc& d = pl->planes[i];
+      if (build_strip_stream(pl->strips, d.height, d.width, d.in_pitch, d.out_pitch, pl->sstreams[i]))
+        pl->sedges = pl->sedges || strip_edges(pl->strips, pl->sstreams[i]);
+      else
+        pl->strips.cls = -1;
+    }
+    // the edge instances hold three workgroups at most (32 frames of 1366x768 at
+    // 1/2, planned for four 43 us, for three 39)
+    if (pl->sedges) pl->strips.resident = std::min(pl->strips.resident, 3);
+    for (int f = 0; f < kStripForms && pl->strips.cls >= 0; ++f) {
+      if (f == kStripWide && pl->sedges) pl->strips.wnb[f] = 0;  // (no such instance)
+      if (!pl->strips.wnb[f]) continue;
+      const hipError_t e = strip_prepare(pl->elem, pl->strips.cls, f, pl->sedges, pl->strips.lds[f]);
+      if (e != hipSuccess) return hip_fail(e, "strip kernel attributes");
+    }
+  }
+  // The band kernel's tables and unit lists go to the device only where it runs
+  // the plan (an I420 1920x1080 plan: nine allocations and copies, 307 us in
+  // all with them, 187 without).
+  const bool bands = pl->strips.cls < 0;
+  if (bands && (st = upload_filter_bands(fb))) return st;
   int lds = 0, slots = 0;
   for (int i = 0; i < pl->n_planes; ++i) {
     int l = 0, sl = 0;
@@ -421,7 +446,7 @@ static aol_status plan_build_band(aol_plan* pl, int xreps, int seg) {
   if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
     return hip_fail(e, "hipDeviceGetAttribute");
   DeviceBuf ds;
-  if ((st = ds.upload(pl->bstreams, sizeof(BandStream) * pl->n_planes))) return st;
+  if (bands && (st = ds.upload(pl->bstreams, sizeof(BandStream) * pl->n_planes))) return st;
   // Segment lengths: the requested one, else about 512, 256, 128 and 64 input
   // lines. Each list holds the units of one frame, most expensive first: a
   // launch over n frames hands its n * units items to the workgroups in
@@ -448,7 +473,7 @@ static aol_status plan_build_band(aol_plan* pl, int xreps, int seg) {
       aol_plan::BandSched sc;
       sc.seg = sg;
       sc.units = (int)sorted.size();
-      if ((st = sc.d_units.upload(sorted.data(), sizeof(BandUnit) * sorted.size()))) return st;
+      if (bands && (st = sc.d_units.upload(sorted.data(), sizeof(BandUnit) * sorted.size()))) return st;
       scheds.push_back(std::move(sc));
       if (seg > 0) break;
     }
@@ -460,26 +485,6 @@ static aol_status plan_build_band(aol_plan* pl, int xreps, int seg) {
   pl->bslots = slots;
   pl->blds = (size_t)lds;
   pl->bgrid = wg * cus;
-  if (pl->strips.cls < 0) {
-    if ((st = build_strip_tables(pl->hf, pl->vf, pl->elem, pl->strips))) return st;
-    pl->sedges = false;
-    for (int i = 0; i < pl->n_planes && pl->strips.cls >= 0; ++i) {
-      const aol_plane_desc& d = pl->planes[i];
-      if (build_strip_stream(pl->strips, d.height, d.width, d.in_pitch, d.out_pitch, pl->sstreams[i]))
-        pl->sedges = pl->sedges || strip_edges(pl->strips, pl->sstreams[i]);
-      else
-        pl->strips.cls = -1;
-    }
-    // the edge instances hold three workgroups at most (32 frames of 1366x768 at
-    // 1/2, planned for four 43 us, for three 39)
-    if (pl->sedges) pl->strips.resident = std::min(pl->strips.resident, 3);
-    for (int f = 0; f < kStripForms && pl->strips.cls >= 0; ++f) {
-      if (f == kStripWide && pl->sedges) pl->strips.wnb[f] = 0;  // (no such instance)
-      if (!pl->strips.wnb[f]) continue;
-      if ((e = strip_prepare(pl->elem, pl->strips.cls, f, pl->sedges, pl->strips.lds[f])) != hipSuccess)
-        return hip_fail(e, "strip kernel attributes");
-    }
-  }
   pl->cus = cus;
   pl->pick.store(0, std::memory_order_relaxed);
   pl->use_band = true;

@@ -178,3 +178,21 @@ got += [seg([(480, 640, 640)] * 5, tune_cache=cache), seg([(480, 640, 1 << 24)] 
 print(json.dumps(got))
 """)
     assert got == [32, 0, 128, 64, 0], got
+
+
+def test_plan_uploads_what_its_kernel_reads(host):
+    """A plan on the strip kernel uploads no unit lists of the column-band kernel (at creation and when a
+    schedule is named); a plan beyond the strip kernel does."""
+    got = host("""
+f = aol.Polyphase(3, 8, synthgen.design_taps(3, 8, 11))
+got = []
+for pitches in (None, [1 << 24]):
+    stub.stub_reset()
+    plan = aol.DownscalePlan([(1080, 1920)], f, f, in_pitches=pitches)
+    got.append(stub.stub_copies())
+    stub.stub_reset()
+    plan.set_band(0, 32)
+    got.append(stub.stub_copies())
+print(json.dumps(got))
+""")
+    assert got[2] - got[0] >= 8 and got[3] - got[1] >= 6, got
