@@ -430,26 +430,20 @@ struct Strip {
     int vlb = B0 - vp * nv, vper = vp * psteps - s0;  // block within the period, the period's first step
     int fire = __builtin_amdgcn_readlane(v1tab, vlb) + vper;
 
-    // Vertical block B from the window ending before step `fire` (from s0).
-    auto vblock = [&]() {
+    // Vertical block B from the window ending before step `fire` (from s0);
+    // r: fire mod NZ, a constant where the step loop is unrolled over the ring.
+    auto vblock = [&](int r) __attribute__((always_inline)) {
       const uint8_t* fl = lds + (vlb * KV * PARTS) * 1024 + lane * 16;
       v4i vf[KV], vfh[SPLIT ? KV : 1];
-      if constexpr (RING) {
+      if constexpr (RING && ELEM == kU8) {
         // the coefficients in the order of the ring's slots: slot d holds
         // window step (d - fire) mod NZ
-        const int r = fire % NZ;
 #pragma unroll
         for (int d = 0; d < NZ; ++d) {
-          const int i = d - r + (d < r ? NZ : 0);  // uniform
-          if constexpr (ELEM == kU8) {
-            const uint8_t* f = fl + (i >> 2) * PARTS * 1024 + (i & 3) * 4;
-            vf[d >> 2][d & 3] = *reinterpret_cast<const int*>(f);
-            if constexpr (SPLIT) vfh[d >> 2][d & 3] = *reinterpret_cast<const int*>(f + 1024);
-          } else {
-            const int2 f = *reinterpret_cast<const int2*>(fl + (i >> 1) * 1024 + (i & 1) * 8);
-            vf[d >> 1][2 * (d & 1)] = f.x;
-            vf[d >> 1][2 * (d & 1) + 1] = f.y;
-          }
+          const int i = d - r + (d < r ? NZ : 0);
+          const uint8_t* f = fl + (i >> 2) * PARTS * 1024 + (i & 3) * 4;
+          vf[d >> 2][d & 3] = *reinterpret_cast<const int*>(f);
+          if constexpr (SPLIT) vfh[d >> 2][d & 3] = *reinterpret_cast<const int*>(f + 1024);
         }
       } else {
 #pragma unroll
@@ -478,17 +472,27 @@ struct Strip {
         }
         store(S, B, y);
       } else {
+        // The low halves first: their sums round at their own small size. The window's
+        // steps in order wherever the ring starts: sums round alike in every schedule.
+        // (Where it starts at an odd slot the operands cross the pairs of slots that are
+        // adjacent registers; an xor with zero copies them, which the compiler would
+        // otherwise do for the whole window at once, in registers it does not have.)
         v4f y[NB];
+        int zero = 0;
+        asm("" : "+s"(zero));
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
-          // the low halves first: their sums round at their own small size
           y[j] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int h = 2; h >= 0; h -= 2)
 #pragma unroll
             for (int k = 0; k < KV; ++k) {
-              const auto &a = z[j][2 * k], &b = z[j][2 * k + 1];
-              y[j] = mfma16<ELEM>(v4i{(int)a[h], (int)a[h + 1], (int)b[h], (int)b[h + 1]}, vf[k], y[j]);
+              const auto &a = z[j][slot(2 * k, r)], &b = z[j][slot(2 * k + 1, r)];
+              v4i x = v4i{(int)a[h], (int)a[h + 1], (int)b[h], (int)b[h + 1]};
+              if (RING && (r & 1))
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] ^= zero;
+              y[j] = mfma16<ELEM>(x, vf[k], y[j]);
             }
         }
         store(S, B, y);
@@ -567,12 +571,15 @@ struct Strip {
               z[j][slot][3] = pack2<ELEM>(r[2] - lo16<ELEM>(h23), r[3] - hi16<ELEM>(h23));
             }
           }
-          while (B < B1 && fire == m + u + 1) vblock();
+          while (B < B1 && fire == m + u + 1) vblock(RING ? (u + 1) % NZ : 0);
         }
         lds_barrier();  // every wave is done with step m + u, the next one is staged
       }
     }
   }
+
+  // Register slot of window step i where the ring starts at r.
+  static __device__ __forceinline__ int slot(int i, int r) { return RING ? (i + r) % NZ : i; }
 
   // The vertical operand of K-step k (integer form): four steps' words.
   static __device__ __forceinline__ v4i zop8(const uint32_t (&w)[NZ][ELEM == kU8 ? 1 : 4], int k) {
