@@ -248,12 +248,14 @@ struct Strip {
     for (int j = 0; j < NB; ++j) {
       const uint32_t e = (uint32_t)F->hblk[lb];
       const int c0 = (int)(e & 0xFFFFu) + per * F->per_chunks - cfirst;
+      const int cend = F->hend[lb] + per * F->per_chunks - cfirst;
       const int f0 = (int)((e >> 16) & 0xFFu), nk = (int)(e >> 24);
 #pragma unroll
       for (int k = 0; k < KH; ++k) {
-        // K-steps and chunks beyond the window: zero coefficients on chunks the step holds
+        // K-steps and chunks beyond the window: zero coefficients on the window's own
+        // chunks (0 * x is not 0 for an infinity or NaN)
         const bool on = k < nk;
-        aoff[j][k] = n * pitch + min(c0 + (on ? 4 * k : 0) + g, nch - 1) * 16;
+        aoff[j][k] = n * pitch + min(c0 + (on ? 4 * k : 0) + g, cend - 1) * 16;
         const int f = (on ? f0 + k : F->zfrag) * PARTS;
         bf[j][k] = *(const STRIP_GLOBAL v4i*)(hf + f * 1024);
         if constexpr (SPLIT) bfh[j][k] = *(const STRIP_GLOBAL v4i*)(hf + f * 1024 + 1024);
@@ -478,6 +480,7 @@ struct Strip {
         // adjacent registers; an xor with zero copies them, which the compiler would
         // otherwise do for the whole window at once, in registers it does not have.)
         v4f y[NB];
+        float sum = 0.f;  // not finite if one of the results is not
         int zero = 0;
         asm("" : "+s"(zero));
 #pragma unroll
@@ -494,6 +497,59 @@ struct Strip {
                 for (int e = 0; e < 4; ++e) x[e] ^= zero;
               y[j] = mfma16<ELEM>(x, vf[k], y[j]);
             }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sum += y[j][i];
+        }
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!__builtin_isfinite(sum)) != 0, 0)) {  // uniform
+          // An infinity or NaN. The window's K-steps hold lines of other blocks too, and
+          // 0 * x is not 0 there: the products again with all lines but the block's own
+          // ones zero, so that a result depends on its block's lines alone, whatever the
+          // schedule. (One product after the other: no registers of the step loop.)
+          const int w0 = 16 * (F->v1[vlb] - NZ), lo = F->vlo[vlb] - w0, n_lines = F->vhi[vlb] - w0 - lo;
+          auto next = [&]() {
+            int at = lane;
+            asm volatile("" : "+v"(at));
+            __builtin_amdgcn_sched_barrier(0);
+            return at;
+          };
+          // mask of word q of window step i: the lines inside the block's window (at: the lane)
+          auto own = [&](int at, int i, int q) {
+            const int t = (at >> 4 << 2) + (16 * i + 2 * (q & 1) - lo);  // the word's first line, from the block's first
+            return ((uint32_t)t < (uint32_t)n_lines ? 0xFFFFu : 0u) |
+                   ((uint32_t)(t + 1) < (uint32_t)n_lines ? 0xFFFF0000u : 0u);
+          };
+#pragma unroll
+          for (int j = 0; j < NB; ++j) {
+            // a window that shifts: masked in place, since no later block reads a line
+            // before this one's first; the last step's lines past the window are put back
+            uint32_t last[ZW];
+            if constexpr (!RING)
+#pragma unroll
+              for (int i = 0; i < NZ; ++i)
+#pragma unroll
+                for (int q = 0; q < ZW; ++q) {
+                  if (i == NZ - 1) last[q] = z[j][i][q];
+                  z[j][i][q] &= own(next(), i, q);
+                }
+            y[j] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int h = 2; h >= 0; h -= 2)
+#pragma unroll
+              for (int k = 0; k < KV; ++k) {
+                const int at = next();
+                v4i x;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                  const int i = 2 * k + (e >> 1);
+                  x[e] = (int)z[j][slot(i, r)][h + (e & 1)];
+                  if constexpr (RING) x[e] &= (int)own(at, i, e & 1);
+                }
+                y[j] = mfma16<ELEM>(x, vf[k], y[j]);
+              }
+            if constexpr (!RING)
+#pragma unroll
+              for (int q = 0; q < ZW; ++q) z[j][NZ - 1][q] = last[q];
+          }
         }
         store(S, B, y);
       }
