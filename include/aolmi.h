@@ -162,9 +162,14 @@ aol_status aol_plan_set_band(aol_plan* plan, int32_t band_reps, int32_t seg_reps
  * 1 = column-major. A schedule choice only; results are identical. */
 aol_status aol_plan_set_walk(aol_plan* plan, int32_t order);
 
-/* The schedule a launch of n_frames frames uses, as a JSON object (kernel,
- * segment length, units per frame, items, grid, LDS bytes); plan-owned text,
- * valid until the next call on the plan. "" for a NULL plan. */
+/* The schedule of a launch of n_frames frames, as a JSON object; plan-owned
+ * text, valid until the next call on the plan. "" for a NULL plan. "kernel" is
+ * "tiled" (after aol_plan_set_tile; its tile and LDS bytes follow) or "band"
+ * (the streaming kernels), with the column bands' segment length, units per
+ * frame, items, grid and LDS bytes, and "runs": the launch that is made, its
+ * kernel ("strip", or "band" for planes of 4 GiB or more), waves per
+ * workgroup, workgroups and LDS bytes, for "strip" also the 16-row output
+ * blocks per segment. */
 const char* aol_plan_schedule(aol_plan* plan, int32_t n_frames);
 
 /* Integer path (plan precision AOL_PREC_U8). For plane j, d_in[j] points to

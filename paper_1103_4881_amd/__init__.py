@@ -328,7 +328,7 @@ class DownscalePlan:
         aol_plan_set_walk(self._h, order)
 
     def schedule(self, n_frames: int) -> dict:
-        """The schedule a launch over ``n_frames`` frames uses."""
+        """The schedule of a launch over ``n_frames`` frames; ``["runs"]`` is the launch itself."""
         import json
         return json.loads(aol_plan_schedule(self._h, n_frames))
 

@@ -694,6 +694,19 @@ static int strip_form(const aol_plan* plan, int n_frames, const aol_plan::BandSc
   return kStripUsual;
 }
 
+// The planes' descriptors of a launch in this form with this many vertical
+// blocks per segment; returns the workgroups of a frame.
+static int64_t strip_streams(const aol_plan* plan, int form, int segb, StripStream* st) {
+  int64_t wgs = 0;
+  for (int i = 0; i < plan->n_planes; ++i) {
+    st[i] = plan->sstreams[i];
+    strip_set_segments(st[i], plan->strips.wnb[form], segb);
+    st[i].wg_base = (int32_t)wgs;
+    wgs += (int64_t)st[i].wgx * st[i].nseg;
+  }
+  return wgs;
+}
+
 static aol_status run_strips(aol_plan* plan, int32_t n_frames, const void* const* d_in, const int64_t* in_fs,
                              void* const* d_out, const int64_t* out_fs, hipStream_t stream) {
   StripLaunch L;
@@ -709,13 +722,8 @@ static aol_status run_strips(aol_plan* plan, int32_t n_frames, const void* const
     plan->pick.store(pick, std::memory_order_relaxed);
   }
   const int form = (int)(pick >> 16 & 0xFFFF), segb = (int)(pick & 0xFFFF);
-  int64_t wgs = 0;
+  const int64_t wgs = strip_streams(plan, form, segb, L.st);
   for (int i = 0; i < plan->n_planes; ++i) {
-    StripStream& S = L.st[i];
-    S = plan->sstreams[i];
-    strip_set_segments(S, plan->strips.wnb[form], segb);
-    S.wg_base = (int32_t)wgs;
-    wgs += (int64_t)S.wgx * S.nseg;
     L.ptrs[2 * i] = d_in[i];
     L.ptrs[2 * i + 1] = d_out[i];
     L.fstride[2 * i] = n_frames > 1 ? in_fs[i] : 0;
@@ -857,7 +865,7 @@ aol_status aol_downscale_u8(aol_plan* plan, int32_t n_frames, const uint8_t* con
 
 const char* aol_plan_schedule(aol_plan* plan, int32_t n_frames) {
   if (!plan) return "";
-  char buf[400];
+  char buf[512];
   if (plan->use_band) {
     const aol_plan::BandSched* sc = band_pick_sched(plan, std::max(1, (int)n_frames));
     const int64_t items = (int64_t)sc->units * std::max(1, (int)n_frames);
@@ -868,11 +876,18 @@ const char* aol_plan_schedule(aol_plan* plan, int32_t n_frames) {
                  sc->seg, sc->units, (long long)items, (long long)std::min<int64_t>(items, plan->bgrid), plan->bslots,
                  plan->fbands.kmax, plan->fbands.split ? 1 : 0, plan->blds);
     if (plan->strips.cls >= 0) {
+      StripStream st[kMaxPlanes];
       int segb = 0;
       const int form = strip_form(plan, std::max(1, (int)n_frames), sc, &segb);
-      snprintf(buf + at, sizeof buf - at, ", \"form\": %d, \"seg_blocks\": %d}", form, segb);
+      const int64_t wgs = strip_streams(plan, form, segb, st) * std::max(1, (int)n_frames);
+      snprintf(buf + at, sizeof buf - at,
+               ", \"form\": %d, \"seg_blocks\": %d, \"runs\": {\"kernel\": \"strip\", \"waves\": %d, \"seg_blocks\": %d, "
+               "\"workgroups\": %lld, \"lds\": %zu}}",
+               form, segb, strip_waves(form), segb, (long long)wgs, plan->strips.lds[form]);
     } else {
-      snprintf(buf + at, sizeof buf - at, "}");
+      snprintf(buf + at, sizeof buf - at,
+               ", \"runs\": {\"kernel\": \"band\", \"waves\": %d, \"workgroups\": %lld, \"lds\": %zu}}",
+               kBandThreads / 64, (long long)std::min<int64_t>(items, plan->bgrid), plan->blds);
     }
   } else {
     snprintf(buf, sizeof buf, "{\"kernel\": \"tiled\", \"tile\": [%d, %d], \"lds\": %zu}", plan->trx, plan->try_,

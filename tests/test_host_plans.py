@@ -196,3 +196,29 @@ for pitches in (None, [1 << 24]):
 print(json.dumps(got))
 """)
     assert got[2] - got[0] >= 8 and got[3] - got[1] >= 6, got
+
+
+def test_schedule_reports_the_launch(host):
+    """The "runs" part of a plan's schedule is the launch that is made."""
+    got = host("""
+f = aol.Polyphase(3, 8, synthgen.design_taps(3, 8, 11))
+got = []
+for shapes, kw in (([(1080, 1920), (540, 960), (540, 960)], {}), ([(768, 1366)], {}), ([(480, 640)], dict(precision="bf16")),
+                   ([(480, 640)], dict(in_pitches=[1 << 24])), ([(480, 640)], dict(seg=32))):
+    seg = kw.pop("seg", 0)
+    plan = aol.DownscalePlan(shapes, f, f, **kw)
+    if seg:
+        plan.set_band(0, seg)
+    for n in (1, 3, 40, 300):
+        stub.stub_reset()
+        fn = aol.aol_downscale_f if kw.get("precision") else aol.aol_downscale_u8
+        k = len(shapes)
+        fn(plan._h, n, [BUF] * k, [1 << 34] * k, [BUF] * k, [1 << 34] * k, 0)
+        got.append([plan.schedule(n)["runs"], launches()])
+print(json.dumps(got))
+""")
+    for runs, made in got:
+        assert len(made) == 1, made
+        name, grid, block = made[0]
+        assert f"k_{runs['kernel']}I" in name and runs["workgroups"] == grid and runs["waves"] * 64 == block, (runs, made)
+    assert {r["kernel"] for r, _ in got} == {"strip", "band"} and {r["waves"] for r, _ in got} == {4, 8, 16}
