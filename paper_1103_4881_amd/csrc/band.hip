@@ -477,7 +477,7 @@ __device__ __forceinline__ void band_unit(const BandLaunch& L, int u, BandStream
 // bands of a segment run on one XCD at the same time and the lines at their
 // shared edges are fetched from memory once.
 __device__ __forceinline__ int band_slot(const BandLaunch& L) {
-  const int G = L.ngroups, g = (int)blockIdx.x - L.wg0;
+  const int G = L.ngroups, g = (int)blockIdx.x;
   return (L.grouped && G % 8 == 0) ? (g % 8) * (G / 8) + g / 8 : g;
 }
 
@@ -490,7 +490,7 @@ __device__ __forceinline__ int band_slot(const BandLaunch& L) {
 // gets a similar mix of long and short units whatever the frame count.
 __device__ __forceinline__ void band_share(const BandLaunch& L, int& i0, int& i1) {
   if (L.order) {
-    const AOL_CONST int32_t* f = (const AOL_CONST int32_t*)L.first + ((int)blockIdx.x - L.wg0);
+    const AOL_CONST int32_t* f = (const AOL_CONST int32_t*)L.first + blockIdx.x;
     i0 = f[0];
     i1 = f[1];
   } else {
@@ -1010,7 +1010,6 @@ hipError_t band_prepare(int elem, int slots, bool split, int kmax, size_t lds_by
 hipError_t band_launch(int elem, int slots, bool split, int kmax, bool gather, const BandLaunch& L, int grid,
                        size_t lds_bytes, hipStream_t stream) {
   BandLaunch La = L;
-  La.wg0 = 0;
   La.ngroups = grid;
   hipLaunchKernelGGL(band_pick(elem, slots, split, kmax, gather), dim3(grid), dim3(kBandThreads), lds_bytes, stream, La);
   return hipGetLastError();
