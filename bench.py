@@ -211,6 +211,8 @@ def bench_unfused(u8, Yh, Uh, Vh, steps, warmup):
 
 LIN_FRAMES = 30
 VALU_MAC_PEAK = 256 * 64 * 2 * 2.4e9  # v_dot2_i32_i16: 2 MACs per lane, a wave64 instruction per CU and cycle
+# v_mfma_i32_16x16x64_i8 (patterns of more than 32 elements): 16 cycles on each of a CU's four SIMDs
+MFMA_I8_MAC_PEAK = 256 * 4 * 16 * 16 * 64 / 16 * 2.4e9
 
 
 def _frames_spec(spec, frames):
@@ -274,8 +276,9 @@ def bench_linear(steps=20, warmup=10, n=LIN_FRAMES):
                      "frac": round(gbs / HBM_PEAK_GBS, 4)},
              "mismatches_first_last_frame": mism}
         tmac = macs / (ms_kernel / 1e3) / 1e12
-        e["alu"] = {"achieved": round(tmac, 2), "peak": round(VALU_MAC_PEAK / 1e12, 1), "unit": "TMAC/s",
-                    "frac": round(tmac * 1e12 / VALU_MAC_PEAK, 4), "macs_per_launch": macs}
+        mac_peak = MFMA_I8_MAC_PEAK if n_in > 32 else VALU_MAC_PEAK
+        e["alu"] = {"achieved": round(tmac, 2), "peak": round(mac_peak / 1e12, 1), "unit": "TMAC/s",
+                    "frac": round(tmac * 1e12 / mac_peak, 4), "macs_per_launch": macs}
         e["bound"] = "hbm" if e["hbm"]["frac"] >= e["alu"]["frac"] else "alu"
         res[name] = e
         log(f"linear {name}: {ms_step:.3f} ms/step, {gbs:.0f} GB/s, {tmac:.1f} TMAC/s, mismatches {mism}")

@@ -143,18 +143,20 @@ aol_status aol_plan_destroy(aol_plan* plan);
  * Rebuilds the plan's tables like aol_plan_set_band (capture graphs again). */
 aol_status aol_plan_set_tile(aol_plan* plan, int32_t tile_rx, int32_t tile_ry);
 
-/* Schedule of the streaming kernels (the default for every plan): workgroups
- * walk segments of seg_reps repetitions down the plane. seg_reps 0: each
- * launch chooses its segments from the frame count. Planes of 4 GiB or more
- * run on column bands of band_reps repetitions (0: the widest that fits a
- * compute unit, normally the full width), the intermediate in an LDS ring;
- * other planes on strips of output columns, the intermediate in registers,
- * for which band_reps is checked only. Multiples of 16. This call (like plan
- * creation) builds and uploads the bands' unit lists synchronously; it frees
- * the previous ones, so a graph captured from an earlier run of this plan must
- * be captured again. It re-selects the streaming kernels after
- * aol_plan_set_tile. AOL_ERR_UNSUPPORTED if the band does not fit. Results
- * are identical for every schedule. */
+/* Schedule of the streaming kernels, the default for every plan that fits them
+ * (the windows of 16 adjacent outputs, on each axis, span at most 256 input
+ * elements, 128 in the float forms, in whole 16-byte chunks; other filters run
+ * tiled): workgroups walk segments of seg_reps repetitions down the plane.
+ * seg_reps 0: each launch chooses its segments from the frame count. Planes of
+ * 4 GiB or more run on column bands of band_reps repetitions (0: the widest
+ * that fits a compute unit, normally the full width), the intermediate in an
+ * LDS ring; other planes on strips of output columns, the intermediate in
+ * registers, for which band_reps is checked only. Multiples of 16. This call
+ * (like plan creation) builds the tables of the kernel that runs the plan and
+ * uploads them synchronously; it frees the previous ones, so a graph captured
+ * from an earlier run of this plan must be captured again. It re-selects the
+ * streaming kernels after aol_plan_set_tile. AOL_ERR_UNSUPPORTED if the band
+ * does not fit. Results are identical for every schedule. */
 aol_status aol_plan_set_band(aol_plan* plan, int32_t band_reps, int32_t seg_reps);
 
 /* Order in which each workgroup walks its contiguous run of tiles inside a
@@ -175,8 +177,11 @@ const char* aol_plan_schedule(aol_plan* plan, int32_t n_frames);
 /* Integer path (plan precision AOL_PREC_U8). For plane j, d_in[j] points to
  * frame 0 of n_frames frames spaced in_frame_stride[j] elements apart, and
  * d_out[j] to the outputs spaced out_frame_stride[j] apart. Host arrays of
- * length n_planes. Vector loads need 16-byte aligned rows and 4-byte aligned
- * output rows; other layouts take a slower element-wise path. */
+ * length n_planes. Any alignment; lines whose width is not a multiple of 16
+ * pixels take a slower path (their ends are joined by byte shifts), and on
+ * planes of 4 GiB or more also buffers, pitches and strides that are not
+ * multiples of 16. Tiled plans load by vector where input rows are 16-byte and
+ * output rows 4-byte aligned, else by element. */
 aol_status aol_downscale_u8(aol_plan* plan, int32_t n_frames, const uint8_t* const* d_in,
                             const int64_t* in_frame_stride, uint8_t* const* d_out,
                             const int64_t* out_frame_stride, hipStream_t stream);

@@ -687,7 +687,7 @@ def aol_batch_set_part_weight(plan, permille: int):
 
 
 class BatchPlan:
-    """Many streams, one frame each per step, one persistent launch (optionally a graph)."""
+    """Many streams, one frame each per step, in one launch, or two (optionally a graph)."""
 
     def __init__(self, streams, precision="u8", tune_cache=None):
         self.precision = precision

@@ -25,7 +25,7 @@ using namespace aol;
 namespace {
 
 struct Schedule {
-  int seg = 0;         // repetitions per segment (0: about 512 input lines)
+  int seg = 0;         // repetitions per segment (0: about 240 input lines, fewer for few streams; column bands 512)
   int budget = 150 * 1024;  // LDS budget per workgroup (picks the column band)
   std::vector<int> class_seg;  // per stream class: its own segment length (0 or absent: seg)
   // Per mille: weight of the int8-tap streams, kept with the schedule and its
@@ -259,8 +259,8 @@ static aol_status batch_strips(aol_batch_plan* bp, const std::vector<int>& rep) 
 // heaviest streams first, each to the XCD with the least work so far. The
 // device hands consecutive workgroups to its 8 XCDs in turn, so the lists are
 // interleaved: neighbours in a row share the lines at their sides through one
-// L2, and the light streams fill the last round. (64 uint8 streams of 320x240
-// to 1920x1080, 237 MB: 68 us, with the workgroups of a row on different XCDs
+// L2, and the light streams fill the last round. (64 uint8 streams of 640x480
+// to 3840x2160, 237 MB: 68 us, with the workgroups of a row on different XCDs
 // 72; where the frames stay in the memory-side cache, 58 against 64.)
 //
 // Segments of 240 input lines (a schedule may name others), shorter ones where

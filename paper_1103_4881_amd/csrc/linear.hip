@@ -500,10 +500,11 @@ __device__ __forceinline__ int __attribute__((ext_vector_type(4))) join16(
   return r;
 }
 
-// Matrix-core form (see LinearBox). What bounds it: the LDS reads of the
-// points' chunks, one 16-byte read per lane and product of 16 points x 16
-// outputs x 64 elements; the point-by-point form spent two byte loads, a pack
-// and n_out dot products per pair of elements and point on the vector units.
+// Matrix-core form (see LinearBox). What bounds it: waits on memory, 58 % of the
+// waves' cycles (the box, and each K-step's weights, which feed two products a
+// part); vector instructions take 17 %, LDS 1 %, without bank conflicts. The
+// point-by-point form spent two byte loads, a pack and n_out dot products per
+// pair of elements and point on the vector units.
 // 30 frames of 1920x1080, 17 x 17 elements to 3 x 3 outputs: 0.239 -> 0.059 ms
 // (blocks of 64 x 4 points 0.062, 64 x 8 0.080, 32 x 16 0.089: small boxes keep
 // more workgroups resident, and their set-up and loads overlap others' products).

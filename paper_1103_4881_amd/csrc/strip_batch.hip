@@ -7,10 +7,11 @@ namespace aol {
 // One workgroup per unit of a batch. Every class of filter is in one kernel, so
 // that streams of different filters share the device in one launch; it holds
 // the registers of its largest class (three workgroups a compute unit). 64
-// uint8 streams of 320x240 to 1920x1080, 237 MB, take 66 us, 3.6 TB/s (one
+// uint8 streams of 640x480 to 3840x2160, 237 MB, take 66 us, 3.6 TB/s (one
 // persistent workgroup per compute unit with a band of columns in LDS: 76 us):
 // about two rounds of workgroups, each with its chain of descriptor loads
-// before its first lines.
+// before its first lines. Its waves wait on memory or LDS 44 % of their cycles
+// and for an issue slot 28 %; 13 % issue vector instructions.
 template <int ELEM, bool EDGES>
 __global__ __launch_bounds__(256, EDGES && ELEM == kU8 ? 2 : 3) void k_strip_batch(StripBatch L) {
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
